@@ -111,9 +111,11 @@ typedef struct tc_ctx tc_ctx;
  * hipStream_t (NULL = default stream).  Waits for the factorisation to
  * finish.  Returns TC_EINVAL for an unsupported grid, TC_ESINGULAR if a
  * pivot is zero or not finite, TC_ENOMEM, TC_EHIP.  *out is NULL on error.
- * On grids of 32, 64 or 128 radial nodes the context also keeps a second,
- * lane-contiguous copy of the factors for the predictor-corrector kernels
- * that hold each mode's radial line on chip; with the environment variable
+ * On grids of up to 64 radial nodes, of up to 128 with at most 65536 distinct
+ * modes m_theta m_z / 2, and of up to 256 with fewer than 16384, the context
+ * also keeps a second, lane-contiguous copy of the factors (while the device
+ * has room for it) for the predictor-corrector and solve kernels that hold
+ * each mode's radial line on chip; with the environment variable
  * TC_PC_LINE=0 set at this call it uses the four-sweep kernels instead (the
  * same results up to rounding) and keeps no copy.  The curl adjoint of
  * tc_step_adjoint runs as radial sweeps on grids with at least 131072

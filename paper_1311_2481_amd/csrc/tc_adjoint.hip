@@ -246,7 +246,15 @@ tc_status ensure_aux(tc_ctx* c) {
     c->aux_bytes = 0;
   }
   void* p = nullptr;
-  if (hipMalloc(&p, need) != hipSuccess) {
+  hipError_t e = hipMalloc(&p, need);
+  if (e != hipSuccess && c->flin) {
+    // no room beside the line kernels' copy of the factors: the four-sweep
+    // kernels take over
+    (void)hipGetLastError();
+    drop_flin(c);
+    e = hipMalloc(&p, need);
+  }
+  if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(c, TC_ENOMEM, "cannot allocate the adjoint work space");
   }

@@ -28,6 +28,13 @@ tc_status hip_check(tc_ctx* c, hipError_t e, const char* what) {
   return fail(c, TC_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+void drop_flin(tc_ctx* c) {
+  (void)hipFree(c->flin);  // waits for the kernels that read it
+  c->flin = nullptr;
+  c->bytes -= c->flin_bytes;
+  c->omega_fresh = false;
+}
+
 void timer_begin(tc_ctx* c, int which) {
   if (!c->timing) return;
   KernelTimer& t = c->timers[which];
@@ -657,13 +664,6 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
   const size_t FB = field_bytes(c);
   c->rc_dev = dev_alloc<double>(c, c->rc.size() * sizeof(double), st);
   c->fac = dev_alloc<double>(c, (size_t)NOPS * d.n_r * NFAC * d.ndm * sizeof(double), st);
-  // the line predictor-corrector where the grid allows it (TC_PC_LINE=0
-  // selects the four-sweep kernels instead)
-  {
-    const char* e = std::getenv("TC_PC_LINE");
-    if (line_lps(d) > 0 && !(e && std::atoi(e) == 0))
-      c->flin = dev_alloc<double>(c, (size_t)NOPS * d.n_r * NFAC * d.ndm * sizeof(double), st);
-  }
   // the curl adjoint as one radial sweep per slot where there are enough
   // slots for the GPU (at least 2048 waves); TC_ADJ_CURL_SWEEP=0 or 1 at
   // this call chooses the tiled or the sweep form on any grid
@@ -694,13 +694,26 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
     c->batch = std::min(c->batch, d.n_r);
     c->inter = dev_alloc<void>(c, per * (size_t)c->batch, st);
   }
+  // the line predictor-corrector where the grid allows it (TC_PC_LINE=0
+  // selects the four-sweep kernels instead); allocated last, and given up
+  // where the device has no room for its copy of the factors
+  {
+    const char* e = std::getenv("TC_PC_LINE");
+    const LineShape ln = line_shape(d);
+    if (st == TC_OK && ln.lps > 0 && !(e && std::atoi(e) == 0)) {
+      const size_t fac = (size_t)NOPS * ln.lps * ln.rpl * NFAC * d.ndm;
+      c->flin_bytes = (fac + (size_t)2 * ln.rpl * LINE_TAB_F * ln.lps) * sizeof(double);
+      tc_status sl = TC_OK;
+      c->flin = dev_alloc<double>(c, c->flin_bytes, sl);
+      if (c->flin) c->ltab = c->flin + fac;
+      else c->err.clear();
+    }
+  }
   if (st != TC_OK) {
     g_init_error = c->err;
     free_ctx(c);
     return st;
   }
-  std::vector<cd> tw;
-  std::vector<cf> twf;
   hipError_t e = hipSuccess;
   auto up = [&](void* dst, const void* src, size_t n) {
     if (e == hipSuccess) e = hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, c->stream);
@@ -721,6 +734,13 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
       wr[j] *= c->r[j];
       Uc[j] = C1 * c->r[j] + C2 / c->r[j];
     }
+  }
+  std::vector<double> ltab;
+  if (c->flin) {
+    // places past the last node stay zero
+    if (e == hipSuccess) e = hipMemsetAsync(c->flin, 0, c->flin_bytes, c->stream);
+    ltab = line_tables(d, c->rc);
+    up(c->ltab, ltab.data(), ltab.size() * sizeof(double));
   }
   up(c->diag_wr, wr.data(), wr.size() * sizeof(double));
   up(c->diag_uc, Uc.data(), Uc.size() * sizeof(double));
@@ -766,7 +786,12 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
     unsigned long long* worst = nullptr;
     unsigned long long hw = 0;
     const size_t tb = (size_t)d.n_r * NOPS * d.ndm * sizeof(double);
-    if (hipMalloc(&tmp, tb) != hipSuccess || hipMalloc(&worst, sizeof(*worst)) != hipSuccess) {
+    if (hipMalloc(&tmp, tb) != hipSuccess && c->flin) {
+      // no room beside the line kernels' copy of the factors: give that up
+      (void)hipGetLastError();
+      drop_flin(c);
+    }
+    if ((!tmp && hipMalloc(&tmp, tb) != hipSuccess) || hipMalloc(&worst, sizeof(*worst)) != hipSuccess) {
       (void)hipGetLastError();
       if (tmp) (void)hipFree(tmp);
       g_init_error = "hipMalloc of the factor check's work space failed";

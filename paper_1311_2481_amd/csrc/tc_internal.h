@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -33,18 +34,27 @@ constexpr int RC_R = 0, RC_IR = 1, RC_IR2 = 2, RC_W1 = 3, RC_W2 = 12, RC_N = 21;
 constexpr int NOPS = 4, NFAC = 9;
 enum { OP_P = 0, OP_HP = 1, OP_HM = 2, OP_HZ = 3 };
 
-// Predictor-corrector with the radial lines on chip (tc_line.hip), for
-// grids of n_r = LINE_RPL * LPS radial nodes with LPS ("lanes per slot") a
-// power of two: lane k of a slot's LPS lanes holds rows LINE_RPL k ..
-// LINE_RPL k + LINE_RPL - 1.  Its factors (flin) hold the values of fac
-// lane-contiguously: for operator op, distinct mode dm and lane k, LINE_Q
-// pairs of doubles, pair q at
-//   flin[((op * ndm + dm) * LINE_Q + q) * 2 LPS + 2 k + {0, 1}];
-// counting the lane's doubles e = 0 .. 2 LINE_Q - 1 in pair order, e < 32
-// is first-sweep multiplier c = e % 4 of row LINE_RPL k + e / 4, and
-// e = 32 + 5 r + c is the inverse pivot (c = 0) or second-sweep
-// coefficient c (c = 1..4) of row LINE_RPL k + r.
-constexpr int LINE_RPL = 8, LINE_Q1 = 16, LINE_Q = 36;
+// Predictor-corrector with the radial lines on chip (tc_line.hip): lps lanes
+// per slot (a power of two), rpl rows on each, n_r <= lps rpl.  Its factors
+// (flin) hold the values of fac lane-contiguously, the second-sweep
+// coefficients scaled by the row's inverse pivot (L D U^ with unit factors).
+// Place x = rpl k + r (lane k, row r) of a line is node x for P and node
+// lps rpl - 1 - x for the Helmholtz operators, the order of each one's
+// factorisation.  One block of 9 lps rpl doubles per (operator op, distinct
+// mode dm), at (op ndm + dm) 9 lps rpl:
+//   kind 0 (first-sweep multipliers) or 1 (scaled second-sweep
+//   coefficients), coefficient c:  (kind rpl + r) 4 lps + (c / 2) 2 lps + 2 k + c % 2,
+//   the inverse pivot:             8 rpl lps + r lps + k.
+// Nodes past n_r - 1 hold zeros.
+// ltab: per-row tables of the line kernels, entry f of row r of lane k at
+// (r LINE_TAB_F + f) lps + k: 9 D1 weights (first table) or the weights of
+// D1's transpose (second), 1/r, and the row's weights in the inner and outer
+// wall rows of half the vector Laplacian.
+constexpr int LINE_TAB_IR = NB9, LINE_TAB_W0 = NB9 + 1, LINE_TAB_WM = NB9 + 2, LINE_TAB_F = NB9 + 3;
+constexpr int LINE_LPS_MAX = 32;
+struct LineShape {
+  int lps, rpl;  // lps = 0: the grid has more rows than the line kernels take
+};
 
 // Doubles of the static scratch array of tc_get_diag_noalloc (4 MiB per GPU).
 constexpr size_t TC_DIAG_SCRATCH_DOUBLES = (size_t)1 << 19;
@@ -109,6 +119,8 @@ struct tc_ctx {
   double* rc_dev = nullptr;
   double* fac = nullptr;
   double* flin = nullptr;    // lane-contiguous copy of fac (line predictor-corrector only)
+  size_t flin_bytes = 0;
+  double* ltab = nullptr;    // per-row tables of the line kernels (behind flin)
   bool adj_curl_sweep = false;  // curl adjoint as radial sweeps (large grids; see tc_init)
   tc::cd* tw_t = nullptr;   // exp(-2 pi i e / p_theta)
   tc::cd* tw_z = nullptr;   // exp(-2 pi i e / p_z)
@@ -154,22 +166,34 @@ hipError_t launch_factor_check(tc_ctx* c, double* tmp, unsigned long long* worst
 // largest backward error tc_init accepts from that check
 constexpr double TC_FACTOR_CHECK_MAX = 1e-12;
 hipError_t launch_solve(tc_ctx* c, int op, int transposed, const cd* rhs, cd* x);
-// transposed solves of nop (1, or 3 starting at OP_HP) operators on
-// consecutive fields rhs + k F -> x + k F (x may alias rhs)
-hipError_t launch_solve_t(tc_ctx* c, int op0, int nop, const cd* rhs, cd* x);
+// transposed solve on grids without the line kernels (x must not alias rhs)
+hipError_t launch_solve_t(tc_ctx* c, int op, const cd* rhs, cd* x);
 // omega_out (nullable): where the last sweep also writes curl(u_next) on
 // grids where pc_fuses_curl() holds (ignored elsewhere)
 hipError_t launch_pc(tc_ctx* c, const cd* u, const cd* u_prev, const cd* N, cd* N_prev_scratch,
                      cd* u_next, cd* p, int want_p, cd* omega_out);
 bool pc_fuses_curl(const tc_ctx* c);
-// the line predictor-corrector (tc_line.hip): its lanes per slot on this
-// grid (0 where it does not run), and its launch (the arguments of
-// launch_pc; omg NULL: no curl)
-int line_lps(const Dims& d);
+// the line predictor-corrector (tc_line.hip): the shape of a line on this
+// grid, and its launch (the arguments of launch_pc; omg NULL: no curl)
+LineShape line_shape(const Dims& d);
+// the two tables of ltab, from the per-node constants rc
+std::vector<double> line_tables(const Dims& d, const std::vector<double>& rc);
 hipError_t launch_pc_line(tc_ctx* c, const cd* u, const cd* u_prev, const cd* N, const cd* N_prev, cd* u_next,
                           cd* p, int want_p, cd* omg);
-// transposed solves on the line layout (the arguments of launch_solve_t)
-hipError_t launch_solve_t_line(tc_ctx* c, int op0, int nop, const cd* rhs, cd* x);
+// solves of nop operators from op0 on the line layout (x may alias rhs)
+hipError_t launch_solve_line(tc_ctx* c, int op0, int nop, int transposed, const cd* rhs, cd* x);
+// what the per-shape units (tc_line_*.hip) launch
+enum { LINE_PC, LINE_SOLVE, LINE_ADJ };
+struct LineArgs {
+  int what, flag, op0, nop;
+  const cd* in[4];
+  cd* out[4];
+};
+hipError_t run_line_2(tc_ctx* c, const LineArgs& x);
+hipError_t run_line_4(tc_ctx* c, const LineArgs& x);
+hipError_t run_line_8(tc_ctx* c, const LineArgs& x);
+hipError_t run_line_16(tc_ctx* c, const LineArgs& x);
+hipError_t run_line_32(tc_ctx* c, const LineArgs& x);
 // the adjoint step's predictor-corrector part on the line layout: from the
 // cotangents of u^{i+1} (ub) and N^i (nin) to those of u^i (out_u, before
 // the nonlinear term's part), u^{i-1}, N^{i-1} and the total cotangent of
@@ -200,6 +224,9 @@ size_t inter_bytes_per_plane(const tc_ctx* c);
 
 // kinetic energy 1/2 int |u|^2 dV of a velocity (synchronous; uses ctx->red)
 hipError_t energy_of(tc_ctx* c, const cd* u, double& E);
+
+// gives up the line kernels' copy of the factors
+void drop_flin(tc_ctx* c);
 
 // timing helpers (no-ops unless ctx->timing)
 void timer_begin(tc_ctx* c, int which);

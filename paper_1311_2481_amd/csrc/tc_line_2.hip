@@ -1,0 +1,6 @@
+// The line kernels at 2 lanes per slot (see tc_line.hip).
+#include "tc_line_dev.h"
+
+namespace tc {
+hipError_t run_line_2(tc_ctx* c, const LineArgs& x) { return run_rpl<2>(c, x); }
+}  // namespace tc

@@ -56,8 +56,8 @@ __device__ __forceinline__ bool make_lane(const Dims& d, ModeLane& L) {
 }
 
 // ------------------------------------------------------------------ factor
-__global__ void k_factor(const double* __restrict__ rc, double* __restrict__ fac, double* __restrict__ flin, Dims d,
-                         int* bad) {
+__global__ void k_factor(const double* __restrict__ rc, double* __restrict__ fac, double* __restrict__ flin,
+                         LineShape ln, Dims d, int* bad) {
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= NOPS * d.ndm) return;
   const int op = gid / d.ndm, dm = gid - op * d.ndm;
@@ -83,12 +83,15 @@ __global__ void k_factor(const double* __restrict__ rc, double* __restrict__ fac
     for (int c = 1; c <= 4; ++c) sec[c] = (ip + c <= M) ? row[HW + c] : 0.0;
     for (int c = 0; c <= 4; ++c) F[(int64_t)(4 + c) * d.ndm] = sec[c];
     if (flin) {
-      // the same values in the line kernel's lane-contiguous layout
-      const int lps = d.n_r / LINE_RPL, k = j / LINE_RPL, r = j % LINE_RPL;
-      double* Lp = flin + ((int64_t)op * d.ndm + dm) * LINE_Q * 2 * lps + 2 * k;
-      auto put = [&](int e, double x) { Lp[(int64_t)(e / 2) * 2 * lps + (e % 2)] = x; };
-      for (int q = 0; q < 4; ++q) put(4 * r + q, mult[q]);
-      for (int c = 0; c <= 4; ++c) put(4 * LINE_RPL + 5 * r + c, sec[c]);
+      // the same in the line kernels' lane-contiguous layout
+      const int x = rev ? ln.lps * ln.rpl - 1 - j : j, k = x / ln.rpl, r = x % ln.rpl;
+      double* Lp = flin + ((int64_t)op * d.ndm + dm) * NFAC * ln.lps * ln.rpl;
+      auto put = [&](int kind, int c, double x) {
+        Lp[(int64_t)(kind * ln.rpl + r) * 4 * ln.lps + (c / 2) * 2 * ln.lps + 2 * k + c % 2] = x;
+      };
+      for (int q = 0; q < 4; ++q) put(0, q, mult[q]);
+      for (int q = 0; q < 4; ++q) put(1, q, sec[q + 1] * sec[0]);
+      Lp[(int64_t)8 * ln.rpl * ln.lps + r * ln.lps + k] = sec[0];
     }
   }
   if (flag) atomicOr(bad, 1);
@@ -96,8 +99,8 @@ __global__ void k_factor(const double* __restrict__ rc, double* __restrict__ fac
 
 hipError_t launch_factor(tc_ctx* c, int* bad_dev) {
   const int total = NOPS * c->d.ndm;
-  hipLaunchKernelGGL(k_factor, dim3((total + 63) / 64), dim3(64), 0, c->stream, c->rc_dev, c->fac, c->flin, c->d,
-                     bad_dev);
+  hipLaunchKernelGGL(k_factor, dim3((total + 63) / 64), dim3(64), 0, c->stream, c->rc_dev, c->fac, c->flin,
+                     line_shape(c->d), c->d, bad_dev);
   return hipGetLastError();
 }
 
@@ -228,7 +231,8 @@ __global__ __launch_bounds__(64) void k_solve(const double* __restrict__ rc, con
 }
 
 hipError_t launch_solve(tc_ctx* c, int op, int transposed, const cd* rhs, cd* x) {
-  if (transposed) return launch_solve_t(c, op, 1, rhs, x);
+  if (c->flin) return launch_solve_line(c, op, 1, transposed, rhs, x);
+  if (transposed) return launch_solve_t(c, op, rhs, x);
   const int blocks = (c->d.ndm + 63) / 64;
   hipLaunchKernelGGL(k_solve, dim3(blocks), dim3(64), 0, c->stream, c->rc_dev, c->fac, c->d, op, rhs, x);
   return hipGetLastError();
@@ -843,60 +847,48 @@ __global__ __launch_bounds__(64) void k_pc4(TC_PC_ARGS) {
 // Transposed solve A^T x = rhs with A = S^-1 L U (S: the Neumann row scale of
 // P, identity for the Helmholtz operators), in the factor's row order:
 // U^T w = rhs forwards, then L^T v = w backwards, then x = S v.
-// NOP operators at once (ops op0..op0+NOP-1, fields
-// rhs + k F -> x + k F), one mode per lane (the Lane1 layout of the
-// predictor-corrector below).  Rows are taken CH at a time: the loads of a
-// chunk are all issued before its recurrence runs, so a sweep waits for
-// memory once per chunk rather than once per row (small problems, where
-// there are too few waves to hide the latency, are bound by exactly that).
-template <int NOP, int CH>
-__global__ __launch_bounds__(64) void k_solve_tn(const double* __restrict__ fac, Dims d, int op0, const cd* rhs, cd* x) {
+// One mode per lane (the Lane1 layout of the predictor-corrector below).
+// Rows are taken CH at a time: the loads of a chunk are all issued before
+// its recurrence runs, so a sweep waits for memory once per chunk rather
+// than once per row.
+template <int CH>
+__global__ __launch_bounds__(64) void k_solve_tn(const double* __restrict__ fac, Dims d, int op, const cd* rhs, cd* x) {
   Lane1 L;
   if (!make_lane1(d, L)) return;
   const int M = d.n_r - 1;
-  const int64_t F = d.F, S = d.S;
-  // ops 1-3 (Helmholtz) are factored in descending row order, P ascending
-  const bool rev = (op0 != OP_P);
+  const int64_t S = d.S;
+  // the Helmholtz operators are factored in descending row order, P ascending
+  const bool rev = (op != OP_P);
   auto row_of = [&](int ip) { return rev ? M - ip : ip; };
-  auto fw = [&](int op, int ip, int c) { return facp(fac, d, op, row_of(ip))[(int64_t)c * d.ndm + L.dm]; };
-  cd w[NOP][4];
+  auto fw = [&](int ip, int c) { return facp(fac, d, op, row_of(ip))[(int64_t)c * d.ndm + L.dm]; };
+  cd w[4];
 #pragma unroll
-  for (int k = 0; k < NOP; ++k)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) w[k][q] = cz();
+  for (int q = 0; q < 4; ++q) w[q] = cz();
   // U^T w = rhs, in processing order
   for (int ip0 = 0; ip0 <= M; ip0 += CH) {
-    cd r[CH][NOP];
-    double inv[CH][NOP], uc[CH][NOP][4];
+    cd r[CH];
+    double inv[CH], uc[CH][4];
 #pragma unroll
     for (int t = 0; t < CH; ++t) {
       const int ip = ip0 + t;
       if (ip > M) continue;
-      const int j = row_of(ip);
+      r[t] = rhs[row_of(ip) * S + L.o];
+      inv[t] = fw(ip, 4);
 #pragma unroll
-      for (int k = 0; k < NOP; ++k) {
-        r[t][k] = rhs[k * F + j * S + L.o];
-        inv[t][k] = fw(op0 + k, ip, 4);
-#pragma unroll
-        for (int c = 1; c <= 4; ++c) uc[t][k][c - 1] = (ip - c >= 0) ? fw(op0 + k, ip - c, 4 + c) : 0.0;
-      }
+      for (int c = 1; c <= 4; ++c) uc[t][c - 1] = (ip - c >= 0) ? fw(ip - c, 4 + c) : 0.0;
     }
 #pragma unroll
     for (int t = 0; t < CH; ++t) {
       const int ip = ip0 + t;
       if (ip > M) continue;
-      const int j = row_of(ip);
+      cd y = r[t];
 #pragma unroll
-      for (int k = 0; k < NOP; ++k) {
-        cd y = r[t][k];
+      for (int c = 1; c <= 4; ++c) y = cnfma(y, uc[t][c - 1], w[c - 1]);
+      y = cmuls(y, inv[t]);
 #pragma unroll
-        for (int c = 1; c <= 4; ++c) y = cnfma(y, uc[t][k][c - 1], w[k][c - 1]);
-        y = cmuls(y, inv[t][k]);
-#pragma unroll
-        for (int q = 3; q >= 1; --q) w[k][q] = w[k][q - 1];
-        w[k][0] = y;
-        x[k * F + j * S + L.o] = y;
-      }
+      for (int q = 3; q >= 1; --q) w[q] = w[q - 1];
+      w[0] = y;
+      x[row_of(ip) * S + L.o] = y;
     }
   }
   // L^T v = w backwards, then x = S v (S: Neumann row scale of P); the
@@ -904,23 +896,17 @@ __global__ __launch_bounds__(64) void k_solve_tn(const double* __restrict__ fac,
   const bool nyq_lane = (L.dm < d.mt) && (threadIdx.x < 32);
   const int64_t onyq = (int64_t)d.nyq * d.mt + L.dm;
 #pragma unroll
-  for (int k = 0; k < NOP; ++k)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) w[k][q] = cz();
+  for (int q = 0; q < 4; ++q) w[q] = cz();
   for (int ip0 = M; ip0 >= 0; ip0 -= CH) {
-    cd r[CH][NOP];
-    double mc[CH][NOP][4];
+    cd r[CH];
+    double mc[CH][4];
 #pragma unroll
     for (int t = 0; t < CH; ++t) {
       const int ip = ip0 - t;
       if (ip < 0) continue;
-      const int j = row_of(ip);
+      r[t] = x[row_of(ip) * S + L.o];
 #pragma unroll
-      for (int k = 0; k < NOP; ++k) {
-        r[t][k] = x[k * F + j * S + L.o];
-#pragma unroll
-        for (int q = 1; q <= 4; ++q) mc[t][k][q - 1] = (ip + q <= M) ? fw(op0 + k, ip + q, q - 1) : 0.0;
-      }
+      for (int q = 1; q <= 4; ++q) mc[t][q - 1] = (ip + q <= M) ? fw(ip + q, q - 1) : 0.0;
     }
 #pragma unroll
     for (int t = 0; t < CH; ++t) {
@@ -928,31 +914,22 @@ __global__ __launch_bounds__(64) void k_solve_tn(const double* __restrict__ fac,
       if (ip < 0) continue;
       const int j = row_of(ip);
       double scale = 1.0;
-      if (op0 == OP_P && !(j == M && L.zero_mode)) scale = (j == 0) ? d.s0 : (j == M ? d.sM : 1.0);
+      if (op == OP_P && !(j == M && L.zero_mode)) scale = (j == 0) ? d.s0 : (j == M ? d.sM : 1.0);
+      cd y = r[t];
 #pragma unroll
-      for (int k = 0; k < NOP; ++k) {
-        cd y = r[t][k];
+      for (int q = 1; q <= 4; ++q) y = cnfma(y, mc[t][q - 1], w[q - 1]);
 #pragma unroll
-        for (int q = 1; q <= 4; ++q) y = cnfma(y, mc[t][k][q - 1], w[k][q - 1]);
-#pragma unroll
-        for (int q = 3; q >= 1; --q) w[k][q] = w[k][q - 1];
-        w[k][0] = y;
-        x[k * F + j * S + L.o] = cmuls(y, scale);
-        if (nyq_lane) x[k * F + j * S + onyq] = cz();
-      }
+      for (int q = 3; q >= 1; --q) w[q] = w[q - 1];
+      w[0] = y;
+      x[j * S + L.o] = cmuls(y, scale);
+      if (nyq_lane) x[j * S + onyq] = cz();
     }
   }
 }
 
-hipError_t launch_solve_t(tc_ctx* c, int op0, int nop, const cd* rhs, cd* x) {
-  if (c->flin && (nop == 1 || (nop == 3 && op0 == OP_HP))) return launch_solve_t_line(c, op0, nop, rhs, x);
+hipError_t launch_solve_t(tc_ctx* c, int op, const cd* rhs, cd* x) {
   const int blocks = (c->d.ndm + 31) / 32;
-  if (nop == 1)
-    hipLaunchKernelGGL((k_solve_tn<1, 8>), dim3(blocks), dim3(64), 0, c->stream, c->fac, c->d, op0, rhs, x);
-  else if (nop == 3 && op0 == OP_HP)
-    hipLaunchKernelGGL((k_solve_tn<3, 4>), dim3(blocks), dim3(64), 0, c->stream, c->fac, c->d, op0, rhs, x);
-  else
-    return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_solve_tn<8>), dim3(blocks), dim3(64), 0, c->stream, c->fac, c->d, op, rhs, x);
   return hipGetLastError();
 }
 
