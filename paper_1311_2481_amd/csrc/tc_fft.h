@@ -1,4 +1,4 @@
-// Mixed-radix Stockham FFT for gfx950 (radices 8, 4, 2, 3, 5), registers
+// Mixed-radix Stockham FFT for gfx950 (radices 8, 4, 2, 3, 5, 6, 10), registers
 // plus LDS exchanges.
 //
 // A workgroup transforms NF sequences of length L at once, TPF threads per
@@ -27,6 +27,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace tc {
 
 // Aligned to its full size so that LDS and global accesses are single
@@ -51,13 +53,36 @@ struct RadixList {
   int r[24];
 };
 
-constexpr RadixList make_radices(int L) {
+// Radices of a length 2^a 3^b 5^c: as many 8s as fit; a 2 left over goes into
+// a 6 or a 10, two into 6 6 or 6 10, so that few passes (and exchanges) are
+// left: 48 = 8 6, 144 = 8 3 6, 288 = 8 6 6, 480 = 8 10 6.  A 3 or 6 comes
+// last, where there is none an 8: with L / 6 or L / 8 threads a thread then
+// holds 6 or 8 points at the end.  SIX: an 8
+// and a 3 as 4 6 (1536 = 8 8 4 6 instead of 8 8 8 3), which leaves every
+// thread one butterfly in the last pass.
+constexpr RadixList make_radices(int L, bool SIX = false) {
   RadixList rl{0, {}};
-  while (L % 8 == 0) { rl.r[rl.n++] = 8; L /= 8; }
-  while (L % 4 == 0) { rl.r[rl.n++] = 4; L /= 4; }
-  while (L % 2 == 0) { rl.r[rl.n++] = 2; L /= 2; }
-  while (L % 3 == 0) { rl.r[rl.n++] = 3; L /= 3; }
-  while (L % 5 == 0) { rl.r[rl.n++] = 5; L /= 5; }
+  int a = 0, b = 0, c = 0;
+  while (L % 2 == 0) { ++a; L /= 2; }
+  while (L % 3 == 0) { ++b; L /= 3; }
+  while (L % 5 == 0) { ++c; L /= 5; }
+  int six = 0, ten = 0;
+  if (SIX && a % 3 == 0 && a >= 6 && b >= 1) { six = 1; --a; --b; }
+  for (; a >= 3; a -= 3) rl.r[rl.n++] = 8;
+  if (a == 2 && b >= 2 && !six) { six = 2; a = 0; b -= 2; }
+  if (a == 2 && b >= 1 && c >= 1 && !six) { six = 1; ten = 1; a = 0; --b; --c; }
+  if (a == 1 && b >= 1) { six = 1; a = 0; --b; }
+  if (a == 1 && c >= 1) { ten = 1; a = 0; --c; }
+  if (a == 2) rl.r[rl.n++] = 4;
+  if (a == 1) rl.r[rl.n++] = 2;
+  for (; ten > 0; --ten) rl.r[rl.n++] = 10;
+  for (; c > 0; --c) rl.r[rl.n++] = 5;
+  for (; b > 0; --b) rl.r[rl.n++] = 3;
+  for (; six > 0; --six) rl.r[rl.n++] = 6;
+  if (rl.r[rl.n - 1] % 3 != 0 && rl.r[0] == 8) {
+    for (int i = 1; i < rl.n; ++i) rl.r[i - 1] = rl.r[i];
+    rl.r[rl.n - 1] = 8;
+  }
   if (L != 1) rl.n = -1;
   return rl;
 }
@@ -136,6 +161,27 @@ template <int SIGN, typename T> struct Butterfly<5, SIGN, T> {
   }
 };
 
+// 2 M points, M = 3 or 5: the prime-factor form, two M-point transforms and M
+// pairs, input M n1 + 2 n2 and output M k1 + (M + 1) k2 (mod 2 M), no twiddles
+template <int M, int SIGN, typename T> struct ButterflyPair {
+  static __device__ __forceinline__ void run(C2<T>* v) {
+    C2<T> e[M], o[M];
+#pragma unroll
+    for (int n = 0; n < M; ++n) {
+      e[n] = v[(2 * n) % (2 * M)];
+      o[n] = v[(M + 2 * n) % (2 * M)];
+    }
+    Butterfly<M, SIGN, T>::run(e);
+    Butterfly<M, SIGN, T>::run(o);
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+      v[((M + 1) * k) % (2 * M)] = cadd(e[k], o[k]);
+      v[(M + (M + 1) * k) % (2 * M)] = csub(e[k], o[k]);
+    }
+  }
+};
+template <int SIGN, typename T> struct Butterfly<6, SIGN, T> : ButterflyPair<3, SIGN, T> {};
+template <int SIGN, typename T> struct Butterfly<10, SIGN, T> : ButterflyPair<5, SIGN, T> {};
 
 constexpr RadixList reversed(RadixList rl) {
   RadixList o{rl.n, {}};
@@ -162,74 +208,60 @@ template <int L, bool SWZ> __host__ __device__ constexpr int lds_len() {
 }
 
 // Twiddles w^q, q = 1..R-1, of one butterfly, w = W[base] (conjugated for
-// SIGN > 0).  With TC_TW_DERIVE only w, w^2 (and w^4 for radix 8) are
-// loaded and the other powers formed by complex products (a few ulp).
-#ifndef TC_TW_DERIVE
-#define TC_TW_DERIVE 1
-#endif
-template <int R, int SIGN, typename T>
-__device__ __forceinline__ void twiddles(const C2<T>* __restrict__ W, int base, C2<T>* w) {
-  auto ld = [&](int q) {
-    C2<T> x = W[q * base];
-    if (SIGN > 0) x.y = -x.y;
-    return x;
-  };
-  if constexpr (!TC_TW_DERIVE || R == 2) {
+// SIGN > 0).  load() reads the few that are kept, some time before apply()
+// needs them: their latency then passes during the exchange before.  In
+// double only w is read and the powers are formed one after another (w^q =
+// w^(q-1) w, a few ulp), so that only two twiddles are live: register
+// pressure decides the occupancy of the long transforms.  In float w, w^2
+// (and w^4 from radix 6 on) are read and the other powers formed by products.
+template <int R, int SIGN, typename T> struct Twiddle {
+  static constexpr bool CHAIN = sizeof(T) == 8;
+  static constexpr int N = CHAIN ? 1 : (R >= 6 ? 3 : (R == 2 || R == 3 ? 1 : 2));
+  C2<T> w[N];
+  __device__ __forceinline__ void load(const C2<T>* __restrict__ W, int base) {
 #pragma unroll
-    for (int q = 1; q < R; ++q) w[q] = ld(q);
-  } else if constexpr (R == 3) {
-    w[1] = ld(1);
-    w[2] = cmul(w[1], w[1]);
-  } else if constexpr (R == 4) {
-    w[1] = ld(1);
-    w[2] = ld(2);
-    w[3] = cmul(w[1], w[2]);
-  } else if constexpr (R == 5) {
-    w[1] = ld(1);
-    w[2] = ld(2);
-    w[3] = cmul(w[1], w[2]);
-    w[4] = cmul(w[2], w[2]);
-  } else {
-    static_assert(R == 8, "radix");
-    w[1] = ld(1);
-    w[2] = ld(2);
-    w[4] = ld(4);
-    w[3] = cmul(w[1], w[2]);
-    w[5] = cmul(w[1], w[4]);
-    w[6] = cmul(w[2], w[4]);
-    w[7] = cmul(w[3], w[4]);
+    for (int k = 0; k < N; ++k) w[k] = W[(1 << k) * base];
   }
-}
-
-// v[q] *= w^q, q = 1..R-1.  In double with TC_TW_CHAIN the powers are formed
-// one after another (w^q = w^(q-1) w, a few ulp), so that only two twiddles
-// are live: register pressure decides the occupancy of the long transforms.
-#ifndef TC_TW_CHAIN
-#define TC_TW_CHAIN 1
-#endif
-template <int R, int SIGN, typename T>
-__device__ __forceinline__ void apply_twiddles(const C2<T>* __restrict__ W, int base, C2<T>* v) {
-  if constexpr (TC_TW_CHAIN && sizeof(T) == 8 && R > 2) {
-    C2<T> w1 = W[base];
-    if (SIGN > 0) w1.y = -w1.y;
-    C2<T> wq = w1;
-    v[1] = cmul(v[1], w1);
+  // v[q] *= w^q, q = 1..R-1
+  __device__ __forceinline__ void apply(C2<T>* v) const {
+    C2<T> u[N];
 #pragma unroll
-    for (int q = 2; q < R; ++q) {
-      wq = cmul(wq, w1);
-      v[q] = cmul(v[q], wq);
+    for (int k = 0; k < N; ++k) u[k] = SIGN > 0 ? cconj(w[k]) : w[k];
+    v[1] = cmul(v[1], u[0]);
+    if constexpr (CHAIN) {
+      C2<T> wq = u[0];
+#pragma unroll
+      for (int q = 2; q < R; ++q) {
+        wq = cmul(wq, u[0]);
+        v[q] = cmul(v[q], wq);
+      }
+    } else if constexpr (R == 3) {
+      v[2] = cmul(v[2], cmul(u[0], u[0]));
+    } else if constexpr (R > 3) {
+      const C2<T> w3 = cmul(u[0], u[1]);
+      v[2] = cmul(v[2], u[1]);
+      v[3] = cmul(v[3], w3);
+      if constexpr (R == 5) v[4] = cmul(v[4], cmul(u[1], u[1]));
+      if constexpr (R >= 6) {
+        const C2<T> w5 = cmul(u[0], u[2]);
+        v[4] = cmul(v[4], u[2]);
+        v[5] = cmul(v[5], w5);
+        if constexpr (R >= 8) {
+          v[6] = cmul(v[6], cmul(u[1], u[2]));
+          v[7] = cmul(v[7], cmul(w3, u[2]));
+        }
+        if constexpr (R == 10) {
+          v[8] = cmul(v[8], cmul(u[2], u[2]));
+          v[9] = cmul(v[9], cmul(w5, u[2]));
+        }
+      }
     }
-  } else {
-    C2<T> w[R];
-    twiddles<R, SIGN, T>(W, base, w);
-#pragma unroll
-    for (int q = 1; q < R; ++q) v[q] = cmul(v[q], w[q]);
   }
-}
+};
 
-template <typename T, int L, int TPF, int SIGN, bool REV, bool SWZ = false>
+template <typename T, int L, int TPF, int SIGN, bool REV, bool SWZ = false, bool SIX = false, bool EARLY = (L < 1024)>
 struct Fft {
-  static constexpr RadixList RL = REV ? reversed(make_radices(L)) : make_radices(L);
+  static constexpr RadixList RL = REV ? reversed(make_radices(L, SIX)) : make_radices(L, SIX);
   static_assert(RL.n > 0, "unsupported transform length");
   static constexpr int P = RL.n;
   static constexpr int R0 = RL.r[0];
@@ -239,118 +271,43 @@ struct Fft {
   using In = C2<T>[PER0][R0];
   using Out = C2<T>[PERN][RN];
 
-  // middle pass P0 (0 < P0 < P-1): LDS src -> LDS dst
-  template <int NF, int PP>
-  static __device__ __forceinline__ void mid(const C2<T>* src, C2<T>* dst, const C2<T>* __restrict__ W, int t, int f,
-                                             bool inplace) {
-    constexpr int R = RL.r[PP];
+  // twiddles of one butterfly of pass PP
+  template <int PP> using Tw = Twiddle<RL.r[PP < P ? PP : P - 1], SIGN, T>;
+
+  // twiddles of this thread's butterflies of pass PP
+  template <int PP, int PER>
+  static __device__ __forceinline__ void load_twiddles(Tw<PP> (&tw)[PER], const C2<T>* __restrict__ W, int t) {
+    constexpr int R = RL.r[PP], NS = radix_product(RL, PP), NB = L / R;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int j = t + k * TPF;
+      // (past the last butterfly: any place of the table)
+      tw[k].load(W, (NB % TPF == 0 || j < NB ? j % NS : 0) * (L / (NS * R)));  // q (j % NS) L/(NS R) < L
+    }
+  }
+
+  // EARLY: a pass's twiddles are read before the exchange in front of it; the
+  // long transforms, whose registers are capped for occupancy, read them at
+  // their use.
+
+  // Pass PP and those after it.  v: the inputs of pass PP (element j + q
+  // L/R, j = t + k TPF), tw: its twiddles (none for the first pass).  Each
+  // exchange goes through buf (lds_len<L>() * NF elements), whole elements
+  // at a time, or, SPLIT, one component at a time through a buffer of T
+  // (half the bytes, twice the barriers): the real parts are written in this
+  // pass's output order and read in the next pass's input order, then the
+  // imaginary parts.
+  template <int NF, bool SPLIT, int PP, int PER, int R>
+  static __device__ __forceinline__ void pass(C2<T> (&v)[PER][R], Tw<PP> (&tw)[PER], Out& vn, void* buf,
+                                              const C2<T>* __restrict__ W, int t, int f) {
     constexpr int NS = radix_product(RL, PP);
     constexpr int NB = L / R;
-    constexpr int PER = (NB + TPF - 1) / TPF;
-    C2<T> v[PER][R];
+    if constexpr (PP > 0 && !EARLY) load_twiddles<PP, PER>(tw, W, t);
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int j = t + k * TPF;
       if (NB % TPF == 0 || j < NB) {
-#pragma unroll
-        for (int q = 0; q < R; ++q) v[k][q] = src[lds_slot<L, SWZ>(j + q * NB) * NF + f];
-      }
-    }
-    if (inplace) __syncthreads();
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int j = t + k * TPF;
-      if (NB % TPF == 0 || j < NB) {
-        const int kk = j % NS;
-        apply_twiddles<R, SIGN, T>(W, kk * (L / (NS * R)), v[k]);  // q kk L/(NS R) < L
-        Butterfly<R, SIGN, T>::run(v[k]);
-        const int base = (j / NS) * NS * R + kk;
-#pragma unroll
-        for (int s = 0; s < R; ++s) dst[lds_slot<L, SWZ>(base + s * NS) * NF + f] = v[k][s];
-      }
-    }
-    __syncthreads();
-  }
-
-  template <int NF, int PP>
-  static __device__ __forceinline__ void mids(C2<T>* a, C2<T>* b, const C2<T>* __restrict__ W, int t, int f,
-                                              bool inplace) {
-    if constexpr (PP < P - 1) {
-      mid<NF, PP>(a, b, W, t, f, inplace);
-      mids<NF, PP + 1>(b, a, W, t, f, inplace);
-    }
-  }
-
-  // buffer the data ends in after the middle passes (for the last pass)
-  static constexpr bool ENDS_IN_B = ((P - 2) % 2) == 1;
-
-  // Full transform.  a, b: LDS buffers of lds_len<L>() * NF elements each
-  // (b may equal a: in-place mode, two barriers per exchange).  Ends with a
-  // barrier, so the buffers may be reused at once.
-  template <int NF>
-  static __device__ __forceinline__ void run(In& v0, Out& vn, C2<T>* a, C2<T>* b, const C2<T>* __restrict__ W, int t,
-                                             int f) {
-    const bool inplace = (a == b);
-    if constexpr (P == 1) {
-#pragma unroll
-      for (int k = 0; k < PER0; ++k) {
-        Butterfly<R0, SIGN, T>::run(v0[k]);
-#pragma unroll
-        for (int s = 0; s < R0; ++s) vn[k][s] = v0[k][s];
-      }
-      return;
-    } else {
-      // first pass: NS = 1, no twiddles; outputs j R0 + s
-      {
-        constexpr int NB = L / R0;
-#pragma unroll
-        for (int k = 0; k < PER0; ++k) {
-          const int j = t + k * TPF;
-          if (NB % TPF == 0 || j < NB) {
-            Butterfly<R0, SIGN, T>::run(v0[k]);
-#pragma unroll
-            for (int s = 0; s < R0; ++s) a[lds_slot<L, SWZ>(j * R0 + s) * NF + f] = v0[k][s];
-          }
-        }
-        __syncthreads();
-      }
-      mids<NF, 1>(a, b, W, t, f, inplace);
-      // last pass: NS = L / RN; outputs j + s L/RN
-      {
-        const C2<T>* src = ENDS_IN_B ? b : a;
-        constexpr int NS = L / RN;
-        constexpr int NB = L / RN;
-#pragma unroll
-        for (int k = 0; k < PERN; ++k) {
-          const int j = t + k * TPF;
-          if (NB % TPF == 0 || j < NB) {
-#pragma unroll
-            for (int q = 0; q < RN; ++q) vn[k][q] = src[lds_slot<L, SWZ>(j + q * NB) * NF + f];
-            apply_twiddles<RN, SIGN, T>(W, j * (L / (NS * RN)), vn[k]);
-            Butterfly<RN, SIGN, T>::run(vn[k]);
-          }
-        }
-        __syncthreads();
-      }
-    }
-  }
-
-  // The same transform with each LDS exchange done one component at a time
-  // through a buffer of T (half the bytes of the complex buffer): the real
-  // parts are written in this pass's output order and read in the next
-  // pass's input order, then the imaginary parts.  Four barriers per
-  // exchange instead of two, for half the LDS.  v: the inputs of pass PP
-  // (element j + q L/R, j = t + k TPF); buf: lds_len<L>() * NF elements.
-  template <int NF, int PP, int PER, int R>
-  static __device__ __forceinline__ void pass_split(C2<T> (&v)[PER][R], Out& vn, T* buf, const C2<T>* __restrict__ W,
-                                                    int t, int f) {
-    constexpr int NS = radix_product(RL, PP);
-    constexpr int NB = L / R;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int j = t + k * TPF;
-      if (NB % TPF == 0 || j < NB) {
-        if constexpr (PP > 0) apply_twiddles<R, SIGN, T>(W, (j % NS) * (L / (NS * R)), v[k]);
+        if constexpr (PP > 0) tw[k].apply(v[k]);
         Butterfly<R, SIGN, T>::run(v[k]);
       }
     }
@@ -364,15 +321,23 @@ struct Fft {
       constexpr int NB2 = L / R2;
       constexpr int PER2 = (NB2 + TPF - 1) / TPF;
       C2<T> nx[PER2][R2];
+      Tw<PP + 1> tw2[PER2];
+      if constexpr (EARLY) load_twiddles<PP + 1, PER2>(tw2, W, t);
+      using E = typename std::conditional<SPLIT, T, C2<T>>::type;
+      E* b = reinterpret_cast<E*>(buf);
 #pragma unroll
-      for (int comp = 0; comp < 2; ++comp) {
+      for (int comp = 0; comp < (SPLIT ? 2 : 1); ++comp) {
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
           const int j = t + k * TPF;
           if (NB % TPF == 0 || j < NB) {
             const int base = (j / NS) * NS * R + j % NS;
 #pragma unroll
-            for (int s = 0; s < R; ++s) buf[lds_slot<L, SWZ>(base + s * NS) * NF + f] = comp ? v[k][s].y : v[k][s].x;
+            for (int s = 0; s < R; ++s) {
+              E& x = b[lds_slot<L, SWZ>(base + s * NS) * NF + f];
+              if constexpr (SPLIT) x = comp ? v[k][s].y : v[k][s].x;
+              else x = v[k][s];
+            }
           }
         }
         __syncthreads();
@@ -382,21 +347,24 @@ struct Fft {
           if (NB2 % TPF == 0 || j < NB2) {
 #pragma unroll
             for (int q = 0; q < R2; ++q) {
-              const T x = buf[lds_slot<L, SWZ>(j + q * NB2) * NF + f];
-              if (comp) nx[k][q].y = x;
-              else nx[k][q].x = x;
+              const E x = b[lds_slot<L, SWZ>(j + q * NB2) * NF + f];
+              if constexpr (SPLIT) (comp ? nx[k][q].y : nx[k][q].x) = x;
+              else nx[k][q] = x;
             }
           }
         }
         __syncthreads();
       }
-      pass_split<NF, PP + 1, PER2, R2>(nx, vn, buf, W, t, f);
+      pass<NF, SPLIT, PP + 1, PER2, R2>(nx, tw2, vn, buf, W, t, f);
     }
   }
-  template <int NF>
-  static __device__ __forceinline__ void run_split(In& v0, Out& vn, T* buf, const C2<T>* __restrict__ W, int t,
-                                                   int f) {
-    pass_split<NF, 0, PER0, R0>(v0, vn, buf, W, t, f);
+
+  // Full transform.  buf: LDS, lds_len<L>() * NF elements of C2<T> (T when
+  // SPLIT).  Every exchange ends with a barrier, so buf may be reused at once.
+  template <int NF, bool SPLIT = false>
+  static __device__ __forceinline__ void run(In& v0, Out& vn, void* buf, const C2<T>* __restrict__ W, int t, int f) {
+    Tw<0> none[PER0];
+    pass<NF, SPLIT, 0, PER0, R0>(v0, none, vn, buf, W, t, f);
   }
 
   // element index held in register slot [k][q] before / after the transform

@@ -220,12 +220,31 @@ template <typename T, int L> struct ZShape {
   static constexpr int WAVES = SPLIT ? 8 : 0;
 };
 // theta kernel: TPF threads per row, RPB rows per workgroup, the LDS
-// exchanges in place (two barriers each).
+// exchanges in place (two barriers each).  WAVE: rows whose threads fit a
+// wave (and leave at most a quarter of it idle), in workgroups of one wave:
+// no row waits for another's loads or barriers (theta 48: 12.9 -> 9.2 us on
+// 32 x 16 x 32, float 192: 33 -> 24 us on 64 x 64 x 128).
 template <typename T, int L> struct TShape {
   static constexpr int TPF = (L % 6 == 0) ? L / 6 : L / 8;
   static constexpr bool FIREV = false;  // radix order of the inverse transform
-  static constexpr int RPB = TPF >= 256 ? 1 : 256 / TPF;
-  static constexpr size_t LDS = (size_t)lds_len<L, false>() * RPB * sizeof(C2<T>);
+  static constexpr bool WAVE = TPF <= 64 && 64 / TPF * TPF >= 48;
+  static constexpr int RPB = WAVE ? 64 / TPF : (TPF >= 256 ? 1 : 256 / TPF);
+  static constexpr int NF = WAVE ? 1 : RPB;  // rows interleaved in LDS
+  static constexpr int LEN = lds_len<L, false>();
+  static constexpr size_t LDS = (size_t)LEN * RPB * sizeof(C2<T>);
+  static constexpr bool PARK = L >= 1024 && L % 6 == 0;  // adjoint: one real field of the row behind it
+  static constexpr size_t LDS_ADJ = LDS + (PARK ? (size_t)L * RPB * sizeof(T) : 0);
+  // Waves per SIMD the long kernels' registers are cut to, by the points a
+  // thread holds of each spectrum (6, or 8 where the length is no multiple of
+  // 6): as many as fit without a spill, or nearly (a few spilled registers
+  // cost more than the wave they buy).  0: the compiler's choice.
+  static constexpr bool LONG = L >= 1024, SIXPT = L % 6 == 0, F64 = sizeof(T) == 8;
+  static constexpr int EU = LONG ? (F64 ? (SIXPT ? 4 : 3) : (SIXPT ? 6 : 4)) : 1;
+  static constexpr int EU_ADJ = LONG ? (SIXPT ? 3 : 2) : 1;
+  static constexpr int EU_CONV = L % 5 == 0 && !SIXPT ? 1 : 2;
+  // row and place of a thread, and its row's LDS
+  static __device__ __forceinline__ int row() { return WAVE ? threadIdx.x / TPF : threadIdx.x % RPB; }
+  static __device__ __forceinline__ int place() { return WAVE ? threadIdx.x % TPF : threadIdx.x / RPB; }
 };
 
 // Output weight of the forward z kernel for field fld at azimuthal index n:
@@ -261,7 +280,6 @@ __attribute__((amdgpu_waves_per_eu(ZShape<T, L>::WAVES > 0 ? ZShape<T, L>::WAVES
   constexpr int NF = Z::NF, TPF = Z::TPF;
   using FI = Fft<T, L, TPF, +1, false, Z::SWZ>;
   extern __shared__ unsigned char lds_raw[];
-  C2<T>* buf = reinterpret_cast<C2<T>*>(lds_raw);
   const int tiles = (d.mt + NF - 1) / NF;
   const int ntiles = tiles * io.nfields * nplanes;
   const int f = threadIdx.x % NF, t = threadIdx.x / NF;
@@ -280,11 +298,16 @@ __attribute__((amdgpu_waves_per_eu(ZShape<T, L>::WAVES > 0 ? ZShape<T, L>::WAVES
         if (e < h) sl = e;
         else if (e > L - h) sl = d.mz - (L - e);
         raw[k][q] = (sl >= 0 && n < d.mt && FI::in_valid(t, k)) ? src[(int64_t)sl * d.mt] : cd{0.0, 0.0};
-        if (io.mulb[fld]) {  // i b v, b = l k_z: the axial derivative
-          const double bb = (double)(sl < h ? sl : sl - d.mz) * d.kz;
+      }
+    if (io.mulb[fld])  // i b v, b = l k_z: the axial derivative (zero where the load was)
+#pragma unroll
+      for (int k = 0; k < FI::PER0; ++k)
+#pragma unroll
+        for (int q = 0; q < FI::R0; ++q) {
+          const int e = FI::in_index(t, k, q);
+          const double bb = (double)(e < h ? e : e - L) * d.kz;
           raw[k][q] = cd{-bb * raw[k][q].y, bb * raw[k][q].x};
         }
-      }
   };
   auto transform_store = [&](int id, cd (&raw)[FI::PER0][FI::R0]) {
     typename FI::In v0;
@@ -293,8 +316,7 @@ __attribute__((amdgpu_waves_per_eu(ZShape<T, L>::WAVES > 0 ? ZShape<T, L>::WAVES
     for (int k = 0; k < FI::PER0; ++k)
 #pragma unroll
       for (int q = 0; q < FI::R0; ++q) v0[k][q] = C2<T>{T(raw[k][q].x), T(raw[k][q].y)};
-    if constexpr (Z::SPLIT) FI::template run_split<NF>(v0, vo, reinterpret_cast<T*>(lds_raw), W, t, f);
-    else FI::template run<NF>(v0, vo, buf, buf, W, t, f);
+    FI::template run<NF, Z::SPLIT>(v0, vo, lds_raw, W, t, f);
     const int tile = id % tiles, rest = id / tiles;
     const int fld = rest % io.nfields, pl = rest / io.nfields;
     const int n = tile * NF + f;
@@ -341,32 +363,79 @@ __attribute__((amdgpu_waves_per_eu(ZShape<T, L>::WAVES > 0 ? ZShape<T, L>::WAVES
   transform_store(id, cur);
 }
 
+// Input of an azimuthal inverse transform from two stored rows A, B of modes n
+// = 0 .. mt - 1:
+//   SPEC_PAIR    the +- pair of a complex field v_r + i v_theta: A[n] for n > 0,
+//                conj(B[-n]) for n < 0, (A[0] + conj(B[0])) m0 at n = 0
+//   SPEC_PACKED  two real fields, x from A and y from B, packed as x + i sy y
+//   SPEC_ONE     A[n] for n >= 0 alone
+// and, for dth != 0, the (first) field multiplied by i n dth.  Elements are
+// loaded without a branch, from place 0 where their mode is not stored, and
+// what depends on a value comes after the last load of its group: with the
+// load and the conjugation of each element under its own conditions the
+// loads waited for one another, half of the kernel's time at 1536 points.
+// A packed spectrum goes in two halves, to bound the registers.
+enum { SPEC_PAIR, SPEC_PACKED, SPEC_ONE };
+template <typename F, typename T, int L, int KIND>
+__device__ __forceinline__ void load_spectrum(typename F::In& v, const C2<T>* __restrict__ A,
+                                              const C2<T>* __restrict__ B, int mt, bool valid, int t, T m0, T sy,
+                                              T dth) {
+  constexpr int G = KIND == SPEC_PACKED && F::R0 % 2 == 0 ? F::R0 / 2 : F::R0;
+  C2<T> b0 = {T(0), T(0)};
+  if constexpr (KIND == SPEC_PAIR) b0 = B[0];
+#pragma unroll
+  for (int k = 0; k < F::PER0; ++k)
+#pragma unroll
+    for (int q0 = 0; q0 < F::R0; q0 += G) {
+      C2<T> y[G];
+#pragma unroll
+      for (int q = q0; q < q0 + G; ++q) {
+        const int e = F::in_index(t, k, q), n = e <= L / 2 ? e : e - L, an = n < 0 ? -n : n;
+        const int at = an < mt ? an : 0;
+        v[k][q] = (KIND == SPEC_PAIR && n < 0 ? B : A)[at];
+        if constexpr (KIND == SPEC_PACKED) y[q - q0] = B[at];
+      }
+#pragma unroll
+      for (int q = q0; q < q0 + G; ++q) {
+        const int e = F::in_index(t, k, q), n = e <= L / 2 ? e : e - L, an = n < 0 ? -n : n;
+        C2<T> x = v[k][q];
+        if constexpr (KIND == SPEC_PAIR) {
+          if (n < 0) x = cconj(x);
+          if (q == 0 && n == 0) x = {m0 * (x.x + b0.x), m0 * (x.y - b0.y)};
+          if (dth != T(0)) x = {-(n * dth) * x.y, (n * dth) * x.x};
+        } else if constexpr (KIND == SPEC_PACKED) {
+          C2<T> w = y[q - q0];
+          if (dth != T(0)) x = {-(an * dth) * x.y, (an * dth) * x.x};
+          if (n < 0) {
+            x = cconj(x);
+            w = cconj(w);
+          }
+          x = (q == 0 && n == 0) ? C2<T>{x.x, sy * w.x} : C2<T>{x.x - sy * w.y, x.y + sy * w.x};
+        }
+        const bool in = valid && an < mt && F::in_valid(t, k) && (KIND != SPEC_ONE || n >= 0);
+        v[k][q] = in ? x : C2<T>{T(0), T(0)};
+      }
+      if constexpr (G < F::R0) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // ------------------------------------------------------------------ theta pass
 template <typename T, int L>
-// Register budget of the theta kernel at lengths >= 1024: in double 4 waves
-// per SIMD (128 VGPRs), at the cost of a small spill measured faster than
-// the unconstrained 3 waves; in float 6 waves.  Shorter rows keep the
-// compiler's choice.
-#ifndef TC_THETA_WAVES
-#define TC_THETA_WAVES 4
-#endif
-__global__ __launch_bounds__((TShape<T, L>::TPF * TShape<T, L>::RPB))
-#if TC_THETA_WAVES
-__attribute__((amdgpu_waves_per_eu(L >= 1024 ? (sizeof(T) == 8 ? TC_THETA_WAVES : 6) : 1)))
-#endif
+__global__ __launch_bounds__((TShape<T, L>::TPF * TShape<T, L>::RPB)) __attribute__((amdgpu_waves_per_eu(TShape<T, L>::EU)))
 void k_theta(Dims d, int nplanes, C2<T>* __restrict__ inter, const C2<T>* __restrict__ W,
              const unsigned int* __restrict__ zmax) {
   using TS = TShape<T, L>;
   constexpr int TPF = TS::TPF, RPB = TS::RPB;
-  using FI = Fft<T, L, TPF, +1, TS::FIREV>;
-  using FF = Fft<T, L, TPF, -1, !TS::FIREV>;
+  // (float and the other azimuthal kernels spill with the 4 6 tail)
+  constexpr bool SIX = sizeof(T) == 8 && L >= 1024;
+  using FI = Fft<T, L, TPF, +1, TS::FIREV, false, SIX>;
+  using FF = Fft<T, L, TPF, -1, !TS::FIREV, false, SIX>;
   static_assert(FI::RN == FF::R0 && FI::PERN == FF::PER0, "mirrored transforms must line up");
   extern __shared__ unsigned char lds_raw[];
-  C2<T>* bufa = reinterpret_cast<C2<T>*>(lds_raw);
-  C2<T>* bufb = bufa;
-  const int f = threadIdx.x % RPB, t = threadIdx.x / RPB;
+  const int lrow = TS::row(), t = TS::place(), f = TS::WAVE ? 0 : lrow;
+  C2<T>* bufa = reinterpret_cast<C2<T>*>(lds_raw) + (TS::WAVE ? lrow * TS::LEN : 0);
   const int64_t rows = (int64_t)nplanes * d.pz;
-  const int64_t row = (int64_t)blockIdx.x * RPB + f;
+  const int64_t row = (int64_t)blockIdx.x * RPB + lrow;
   const bool valid = row < rows;
   const int pl = valid ? (int)(row / d.pz) : 0;
   const int z = valid ? (int)(row - (int64_t)pl * d.pz) : 0;
@@ -374,45 +443,9 @@ void k_theta(Dims d, int nplanes, C2<T>* __restrict__ inter, const C2<T>* __rest
   C2<T>* base = inter + (int64_t)pl * 6 * fstride + (int64_t)z * d.mt;
   const int mt = d.mt;
 
-  // spectrum of h_u (which 0), h_omega (1) or g = u_z + i omega_z (2) at
-  // azimuthal index e (n = e or e - L)
-  // which = 2: g = u_z + i sw omega_z (sw: see below)
-  auto spec = [&](int which, int e, T sw) -> C2<T> {
-    const C2<T>* A = base + (int64_t)(which == 0 ? 0 : (which == 1 ? 3 : 2)) * fstride;
-    const C2<T>* B = base + (int64_t)(which == 0 ? 1 : (which == 1 ? 4 : 5)) * fstride;
-    const int nn = (e <= L / 2) ? e : e - L;
-    C2<T> v = {T(0), T(0)};
-    if (!valid) return v;
-    if (which < 2) {
-      if (nn > 0 && nn < mt) v = A[nn];
-      else if (nn < 0 && -nn < mt) v = cconj(B[-nn]);
-      else if (nn == 0) {
-        const C2<T> p0 = A[0], m0 = B[0];
-        v = {T(0.5) * (p0.x + m0.x), T(0.5) * (p0.y - m0.y)};
-      }
-    } else {
-      if (nn > 0 && nn < mt) {
-        const C2<T> x = A[nn], y = B[nn];
-        v = {x.x - sw * y.y, x.y + sw * y.x};
-      } else if (nn < 0 && -nn < mt) {
-        const C2<T> x = cconj(A[-nn]), y = cconj(B[-nn]);
-        v = {x.x - sw * y.y, x.y + sw * y.x};
-      } else if (nn == 0) {
-        v = {A[0].x, sw * B[0].x};
-      }
-    }
-    return v;
-  };
   typename FI::In v0;
   typename FI::Out hu, hw, g;
-  auto inverse = [&](int which, typename FI::Out& out, T sw) {
-#pragma unroll
-    for (int k = 0; k < FI::PER0; ++k)
-#pragma unroll
-      for (int q = 0; q < FI::R0; ++q)
-        v0[k][q] = FI::in_valid(t, k) ? spec(which, FI::in_index(t, k, q), sw) : C2<T>{T(0), T(0)};
-    FI::template run<RPB>(v0, out, bufa, bufb, W, t, f);
-  };
+  auto fld = [&](int k) { return base + (int64_t)k * fstride; };
   // g carries u_z and omega_z in one complex transform, whose rounding error
   // delta follows its larger part.  In the products, u_z's error is weighted
   // by |h_omega| and omega_z's by |h_u|, so with g = u_z + i sw omega_z the
@@ -437,9 +470,13 @@ void k_theta(Dims d, int nplanes, C2<T>* __restrict__ inter, const C2<T>* __rest
     }
   }
   const T sw = ldexp(T(1), ez), isw = ldexp(T(1), -ez);
-  inverse(0, hu, T(1));
-  inverse(1, hw, T(1));
-  inverse(2, g, sw);
+  // (g first: its two rows per element are loaded while nothing else is held)
+  load_spectrum<FI, T, L, SPEC_PACKED>(v0, fld(2), fld(5), mt, valid, t, T(0), sw, T(0));
+  FI::template run<TS::NF>(v0, g, bufa, W, t, f);
+  load_spectrum<FI, T, L, SPEC_PAIR>(v0, fld(0), fld(1), mt, valid, t, T(0.5), T(0), T(0));
+  FI::template run<TS::NF>(v0, hu, bufa, W, t, f);
+  load_spectrum<FI, T, L, SPEC_PAIR>(v0, fld(3), fld(4), mt, valid, t, T(0.5), T(0), T(0));
+  FI::template run<TS::NF>(v0, hw, bufa, W, t, f);
   // pointwise products (the slots hold the same points for all three)
   typename FF::In hn, nz;
 #pragma unroll
@@ -452,7 +489,7 @@ void k_theta(Dims d, int nplanes, C2<T>* __restrict__ inter, const C2<T>* __rest
       nz[k][q] = {w.x * a.y - w.y * a.x, T(0)};
     }
   typename FF::Out o;
-  FF::template run<RPB>(hn, o, bufa, bufb, W, t, f);
+  FF::template run<TS::NF>(hn, o, bufa, W, t, f);
   if (valid) {
     C2<T>* Bp = base;
     C2<T>* Bm = base + fstride;
@@ -467,7 +504,7 @@ void k_theta(Dims d, int nplanes, C2<T>* __restrict__ inter, const C2<T>* __rest
           else if (L - e < mt) Bm[L - e] = cconj(o[k][s2]);
         }
   }
-  FF::template run<RPB>(nz, o, bufa, bufb, W, t, f);
+  FF::template run<TS::NF>(nz, o, bufa, W, t, f);
   if (valid) {
     C2<T>* Bz = base + 2 * fstride;
 #pragma unroll
@@ -499,30 +536,27 @@ void k_theta(Dims d, int nplanes, C2<T>* __restrict__ inter, const C2<T>* __rest
 // The products are accumulated as each inverse transform completes, so at
 // most h_u, u_z and the two accumulators are held.  Outputs overwrite
 // fields 0-2 of the row, as in the rotational kernel.
-// (2 waves per SIMD at lengths >= 1024: the six inverse transforms' held
-// fields and accumulators do not fit 3 or 4 waves' budgets without spilling)
-#ifndef TC_THETA_CONV_WAVES
-#define TC_THETA_CONV_WAVES 2
-#endif
 template <int L>
 __global__ __launch_bounds__((TShape<double, L>::TPF * TShape<double, L>::RPB))
-#if TC_THETA_WAVES
-__attribute__((amdgpu_waves_per_eu(L >= 1024 ? TC_THETA_CONV_WAVES : 1)))
-#endif
+__attribute__((amdgpu_waves_per_eu(TShape<double, L>::EU_CONV)))
 void k_theta_conv(Dims d, int plane0, int nplanes, cd* __restrict__ inter, const cd* __restrict__ W,
                   const double* __restrict__ rc) {
   using T = double;
   using TS = TShape<T, L>;
   constexpr int TPF = TS::TPF, RPB = TS::RPB;
-  using FI = Fft<T, L, TPF, +1, TS::FIREV>;
-  using FF = Fft<T, L, TPF, -1, !TS::FIREV>;
+  // early twiddles where they fit without a spill: one butterfly per thread
+  // in the last pass and no radix 5 (288: 500 against 550 us on 128 x 96 x
+  // 320, but 192: 75 against 62 us on 64 x 64 x 128)
+  constexpr RadixList RL = make_radices(L);
+  constexpr bool EARLY = L < 1024 && RL.r[RL.n - 1] >= 6 && L % 5 != 0;
+  using FI = Fft<T, L, TPF, +1, TS::FIREV, false, false, EARLY>;
+  using FF = Fft<T, L, TPF, -1, !TS::FIREV, false, false, EARLY>;
   static_assert(FI::RN == FF::R0 && FI::PERN == FF::PER0, "mirrored transforms must line up");
   extern __shared__ unsigned char lds_raw[];
-  cd* bufa = reinterpret_cast<cd*>(lds_raw);
-  cd* bufb = bufa;
-  const int f = threadIdx.x % RPB, t = threadIdx.x / RPB;
+  const int lrow = TS::row(), t = TS::place(), f = TS::WAVE ? 0 : lrow;
+  cd* bufa = reinterpret_cast<cd*>(lds_raw) + (TS::WAVE ? lrow * TS::LEN : 0);
   const int64_t rows = (int64_t)nplanes * d.pz;
-  const int64_t row = (int64_t)blockIdx.x * RPB + f;
+  const int64_t row = (int64_t)blockIdx.x * RPB + lrow;
   const bool valid = row < rows;
   const int pl = valid ? (int)(row / d.pz) : 0;
   const int z = valid ? (int)(row - (int64_t)pl * d.pz) : 0;
@@ -532,65 +566,20 @@ void k_theta_conv(Dims d, int plane0, int nplanes, cd* __restrict__ inter, const
   const double ir = rc[(int64_t)(plane0 + pl) * RC_N + RC_IR];
   const double kr = d.kt * ir;  // d_theta / r multiplies mode n by i n k_theta / r
 
-  // +- pair (fields fa, fb): spectrum of v_r + i v_theta at signed index nn
-  auto pm = [&](int fa, int fb, int nn) -> cd {
-    const cd* A = base + (int64_t)fa * fstride;
-    const cd* B = base + (int64_t)fb * fstride;
-    if (nn > 0 && nn < mt) return A[nn];
-    if (nn < 0 && -nn < mt) return cconj(B[-nn]);
-    if (nn == 0) {
-      const cd p0 = A[0], m0 = B[0];
-      return cd{0.5 * (p0.x + m0.x), 0.5 * (p0.y - m0.y)};
-    }
-    return cd{0.0, 0.0};
-  };
-  // two real fields packed as x + i y: x from field fa (times i n k_theta / r
-  // when dth), y from field fb
-  auto rr = [&](int fa, bool dth, int fb, int nn) -> cd {
-    const cd* A = base + (int64_t)fa * fstride;
-    const cd* B = base + (int64_t)fb * fstride;
-    const int an = nn < 0 ? -nn : nn;
-    if (an >= mt) return cd{0.0, 0.0};
-    cd x = A[an], y = B[an];
-    if (dth) x = cd{-an * kr * x.y, an * kr * x.x};
-    if (nn == 0) return cd{x.x, y.x};
-    if (nn < 0) {
-      x = cconj(x);
-      y = cconj(y);
-    }
-    return cd{x.x - y.y, x.y + y.x};
-  };
-  // which: 0 h_u, 1 h_r, 2 h_t, 3 h_z, 4 g1, 5 g2
-  auto spec = [&](int which, int e) -> cd {
-    if (!valid) return cd{0.0, 0.0};
-    const int nn = (e <= L / 2) ? e : e - L;
-    switch (which) {
-      case 0: return pm(0, 1, nn);
-      case 1: return pm(3, 4, nn);
-      case 2: {
-        const cd v = pm(0, 1, nn);
-        const double w = nn * kr;
-        return cd{-w * v.y, w * v.x};
-      }
-      case 3: return pm(6, 7, nn);
-      case 4: return rr(2, false, 5, nn);
-      default: return rr(2, true, 8, nn);
-    }
-  };
   typename FI::In v0;
-  auto inverse = [&](int which, typename FI::Out& out) {
-#pragma unroll
-    for (int k = 0; k < FI::PER0; ++k)
-#pragma unroll
-      for (int q = 0; q < FI::R0; ++q)
-        v0[k][q] = FI::in_valid(t, k) ? spec(which, FI::in_index(t, k, q)) : cd{0.0, 0.0};
-    FI::template run<RPB>(v0, out, bufa, bufb, W, t, f);
+  auto pair = [&](int fa, int fb, double dth, typename FI::Out& out) {
+    load_spectrum<FI, T, L, SPEC_PAIR>(v0, base + fa * fstride, base + fb * fstride, mt, valid, t, 0.5, 0.0, dth);
+    FI::template run<TS::NF>(v0, out, bufa, W, t, f);
+  };
+  auto packed = [&](int fa, int fb, double dth, typename FI::Out& out) {
+    load_spectrum<FI, T, L, SPEC_PACKED>(v0, base + fa * fstride, base + fb * fstride, mt, valid, t, 0.0, 1.0, dth);
+    FI::template run<TS::NF>(v0, out, bufa, W, t, f);
   };
   typename FI::Out hu, tmp;
   typename FF::In hn, nz;
   T uz[FI::PERN][FI::RN];
-  inverse(0, hu);
-  inverse(4, tmp);  // u_z + i d_r u_z
+  pair(0, 1, 0.0, hu);
+  packed(2, 5, 0.0, tmp);  // u_z + i d_r u_z
 #pragma unroll
   for (int k = 0; k < FI::PERN; ++k)
 #pragma unroll
@@ -598,12 +587,12 @@ void k_theta_conv(Dims d, int plane0, int nplanes, cd* __restrict__ inter, const
       uz[k][q] = tmp[k][q].x;
       nz[k][q] = {hu[k][q].x * tmp[k][q].y, 0.0};
     }
-  inverse(1, tmp);  // d_r
+  pair(3, 4, 0.0, tmp);  // d_r
 #pragma unroll
   for (int k = 0; k < FI::PERN; ++k)
 #pragma unroll
     for (int q = 0; q < FI::RN; ++q) hn[k][q] = {hu[k][q].x * tmp[k][q].x, hu[k][q].x * tmp[k][q].y};
-  inverse(2, tmp);  // d_theta / r
+  pair(0, 1, kr, tmp);  // d_theta / r
 #pragma unroll
   for (int k = 0; k < FI::PERN; ++k)
 #pragma unroll
@@ -611,7 +600,7 @@ void k_theta_conv(Dims d, int plane0, int nplanes, cd* __restrict__ inter, const
       const T ut = hu[k][q].y;
       hn[k][q] = {fma(ut, tmp[k][q].x, hn[k][q].x), fma(ut, tmp[k][q].y, hn[k][q].y)};
     }
-  inverse(3, tmp);  // d_z
+  pair(6, 7, 0.0, tmp);  // d_z
 #pragma unroll
   for (int k = 0; k < FI::PERN; ++k)
 #pragma unroll
@@ -619,7 +608,7 @@ void k_theta_conv(Dims d, int plane0, int nplanes, cd* __restrict__ inter, const
       const T w = uz[k][q];
       hn[k][q] = {fma(w, tmp[k][q].x, hn[k][q].x), fma(w, tmp[k][q].y, hn[k][q].y)};
     }
-  inverse(5, tmp);  // d_theta u_z / r + i d_z u_z
+  packed(2, 8, kr, tmp);  // d_theta u_z / r + i d_z u_z
 #pragma unroll
   for (int k = 0; k < FI::PERN; ++k)
 #pragma unroll
@@ -631,7 +620,7 @@ void k_theta_conv(Dims d, int plane0, int nplanes, cd* __restrict__ inter, const
       hn[k][q] = {fma(-c, ut, hn[k][q].x), fma(c, ur, hn[k][q].y)};
     }
   typename FF::Out o;
-  FF::template run<RPB>(hn, o, bufa, bufb, W, t, f);
+  FF::template run<TS::NF>(hn, o, bufa, W, t, f);
   if (valid) {
     cd* Bp = base;
     cd* Bm = base + fstride;
@@ -646,7 +635,7 @@ void k_theta_conv(Dims d, int plane0, int nplanes, cd* __restrict__ inter, const
           else if (L - e < mt) Bm[L - e] = cconj(o[k][s2]);
         }
   }
-  FF::template run<RPB>(nz, o, bufa, bufb, W, t, f);
+  FF::template run<TS::NF>(nz, o, bufa, W, t, f);
   if (valid) {
     cd* Bz = base + 2 * fstride;
 #pragma unroll
@@ -679,11 +668,8 @@ void k_theta_conv(Dims d, int plane0, int nplanes, cd* __restrict__ inter, const
 // held at once (3 waves per SIMD at the long lengths: 78.8 ms against 82.9
 // ms for the adjoint step at scale with all five inverse spectra held).
 template <typename T, int L>
-#ifndef TC_THETA_ADJ_WAVES
-#define TC_THETA_ADJ_WAVES 3
-#endif
 __global__ __launch_bounds__((TShape<T, L>::TPF * TShape<T, L>::RPB))
-__attribute__((amdgpu_waves_per_eu(L >= 1024 ? TC_THETA_ADJ_WAVES : 1))) void k_theta_adj(Dims d, int nplanes,
+__attribute__((amdgpu_waves_per_eu(TShape<T, L>::EU_ADJ))) void k_theta_adj(Dims d, int nplanes,
                                                                                      C2<T>* __restrict__ inter,
                                                                                      const C2<T>* __restrict__ W) {
   using TS = TShape<T, L>;
@@ -691,11 +677,10 @@ __attribute__((amdgpu_waves_per_eu(L >= 1024 ? TC_THETA_ADJ_WAVES : 1))) void k_
   using FI = Fft<T, L, TPF, +1, TS::FIREV>;
   using FF = Fft<T, L, TPF, -1, !TS::FIREV>;
   extern __shared__ unsigned char lds_raw[];
-  C2<T>* bufa = reinterpret_cast<C2<T>*>(lds_raw);
-  C2<T>* bufb = bufa;
-  const int f = threadIdx.x % RPB, t = threadIdx.x / RPB;
+  const int lrow = TS::row(), t = TS::place(), f = TS::WAVE ? 0 : lrow;
+  C2<T>* bufa = reinterpret_cast<C2<T>*>(lds_raw) + (TS::WAVE ? lrow * TS::LEN : 0);
   const int64_t rows = (int64_t)nplanes * d.pz;
-  const int64_t row = (int64_t)blockIdx.x * RPB + f;
+  const int64_t row = (int64_t)blockIdx.x * RPB + lrow;
   const bool valid = row < rows;
   const int pl = valid ? (int)(row / d.pz) : 0;
   const int z = valid ? (int)(row - (int64_t)pl * d.pz) : 0;
@@ -703,64 +688,43 @@ __attribute__((amdgpu_waves_per_eu(L >= 1024 ? TC_THETA_ADJ_WAVES : 1))) void k_
   C2<T>* base = inter + (int64_t)pl * 9 * fstride + (int64_t)z * d.mt;
   const int mt = d.mt;
   auto fld = [&](int k) { return base + (int64_t)k * fstride; };
-  // mode: 0 pair (n = 0 averaged), 1 packed real pair, 2 pair (n = 0 summed), 3 one-sided
-  auto spec = [&](int mode, const C2<T>* A, const C2<T>* B, int e) -> C2<T> {
-    const int nn = (e <= L / 2) ? e : e - L;
-    C2<T> v = {T(0), T(0)};
-    if (!valid) return v;
-    if (mode == 0 || mode == 2) {
-      if (nn > 0 && nn < mt) v = A[nn];
-      else if (nn < 0 && -nn < mt) v = cconj(B[-nn]);
-      else if (nn == 0) {
-        const C2<T> p0 = A[0], m0 = B[0];
-        const T w = mode == 0 ? T(0.5) : T(1);
-        v = {w * (p0.x + m0.x), w * (p0.y - m0.y)};
-      }
-    } else if (mode == 1) {
-      if (nn > 0 && nn < mt) {
-        const C2<T> x = A[nn], y = B[nn];
-        v = {x.x - y.y, x.y + y.x};
-      } else if (nn < 0 && -nn < mt) {
-        const C2<T> x = cconj(A[-nn]), y = cconj(B[-nn]);
-        v = {x.x - y.y, x.y + y.x};
-      } else if (nn == 0) {
-        v = {A[0].x, B[0].x};
-      }
-    } else {
-      if (nn >= 0 && nn < mt) v = A[nn];
-    }
-    return v;
-  };
   typename FI::In v0;
-  auto inverse = [&](int mode, const C2<T>* A, const C2<T>* B, typename FI::Out& out) {
-#pragma unroll
-    for (int k = 0; k < FI::PER0; ++k)
-#pragma unroll
-      for (int q = 0; q < FI::R0; ++q)
-        v0[k][q] = FI::in_valid(t, k) ? spec(mode, A, B, FI::in_index(t, k, q)) : C2<T>{T(0), T(0)};
-    FI::template run<RPB>(v0, out, bufa, bufb, W, t, f);
+  auto pair = [&](int fa, int fb, T m0, typename FI::Out& out) {
+    load_spectrum<FI, T, L, SPEC_PAIR>(v0, fld(fa), fld(fb), mt, valid, t, m0, T(0), T(0));
+    FI::template run<TS::NF>(v0, out, bufa, W, t, f);
   };
   // The cotangent transforms first, then omega (whose products are
   // finished and transformed at once, their outputs going to the consumed
   // fields 6, 7), then u; at most h_g, g_z, u_z and one partial product
   // are held between transforms.
   typename FI::Out hg, tmp;
-  T gzr[FI::PERN][FI::RN], uzr[FI::PERN][FI::RN], wzr[FI::PERN][FI::RN], a3x[FI::PERN][FI::RN];
-  inverse(2, fld(6), fld(7), hg);
-  inverse(3, fld(8), fld(8), tmp);
+  T gzr[FI::PERN][FI::RN], wzr[FI::PERN][FI::RN], a3x[FI::PERN][FI::RN];
+  // u_z waits in LDS behind the exchange buffer at the long lengths, whose
+  // registers (3 waves per SIMD) do not hold it without a spill
+  constexpr bool PARK = TS::PARK;
+  T uzr[PARK ? 1 : FI::PERN][FI::RN];
+  T* park = reinterpret_cast<T*>(lds_raw + TS::LDS) + threadIdx.x;
+  auto uz_at = [&](int k, int q) -> T& {
+    if constexpr (PARK) return park[(k * FI::RN + q) * (TPF * RPB)];
+    else return uzr[k][q];
+  };
+  pair(6, 7, T(1), hg);  // n = 0 summed
+  load_spectrum<FI, T, L, SPEC_ONE>(v0, fld(8), fld(8), mt, valid, t, T(0), T(0), T(0));
+  FI::template run<TS::NF>(v0, tmp, bufa, W, t, f);
 #pragma unroll
   for (int k = 0; k < FI::PERN; ++k)
 #pragma unroll
     for (int q = 0; q < FI::RN; ++q) gzr[k][q] = tmp[k][q].x;
-  inverse(1, fld(2), fld(5), tmp);  // u_z + i omega_z
+  load_spectrum<FI, T, L, SPEC_PACKED>(v0, fld(2), fld(5), mt, valid, t, T(0), T(1), T(0));
+  FI::template run<TS::NF>(v0, tmp, bufa, W, t, f);  // u_z + i omega_z
 #pragma unroll
   for (int k = 0; k < FI::PERN; ++k)
 #pragma unroll
     for (int q = 0; q < FI::RN; ++q) {
-      uzr[k][q] = tmp[k][q].x;
+      uz_at(k, q) = tmp[k][q].x;
       wzr[k][q] = tmp[k][q].y;
     }
-  inverse(0, fld(3), fld(4), tmp);  // omega_r + i omega_theta
+  pair(3, 4, T(0.5), tmp);  // omega_r + i omega_theta
   typename FF::In a;
 #pragma unroll
   for (int k = 0; k < FI::PERN; ++k)
@@ -788,37 +752,37 @@ __attribute__((amdgpu_waves_per_eu(L >= 1024 ? TC_THETA_ADJ_WAVES : 1))) void k_
           else if (L - e < mt) Bm[L - e] = cconj(o[k][s2]);
         }
   };
-  FF::template run<RPB>(a, o, bufa, bufb, W, t, f);
+  FF::template run<TS::NF>(a, o, bufa, W, t, f);
   store_pair(6, 7);
-  inverse(0, fld(0), fld(1), tmp);  // u_r + i u_theta
+  pair(0, 1, T(0.5), tmp);  // u_r + i u_theta
   typename FF::In a3;
 #pragma unroll
   for (int k = 0; k < FI::PERN; ++k)
 #pragma unroll
     for (int q = 0; q < FI::RN; ++q) {
-      const T ur = tmp[k][q].x, ut = tmp[k][q].y, uz = uzr[k][q];
+      const T ur = tmp[k][q].x, ut = tmp[k][q].y, uz = uz_at(k, q);
       const T gr = hg[k][q].x, gt = hg[k][q].y, gzv = gzr[k][q];
       // omega_bar = u x g
       a[k][q] = {ut * gzv - uz * gt, uz * gr - ur * gzv};
       a3[k][q] = {a3x[k][q], ur * gt - ut * gr};
     }
-  FF::template run<RPB>(a, o, bufa, bufb, W, t, f);
+  FF::template run<TS::NF>(a, o, bufa, W, t, f);
   store_pair(2, 3);
-  FF::template run<RPB>(a3, o, bufa, bufb, W, t, f);
+  FF::template run<TS::NF>(a3, o, bufa, W, t, f);
   // separate the packed real fields: X(n) = (G(n) + conj G(-n))/2, Y(n) = (G(n) - conj G(-n))/(2i)
   // G(n) and G(-n) sit in different threads: go through LDS
 #pragma unroll
   for (int k = 0; k < FF::PERN; ++k)
     if (FF::out_valid(t, k))
 #pragma unroll
-      for (int s2 = 0; s2 < FF::RN; ++s2) bufa[lds_slot<L, false>(FF::out_index(t, k, s2)) * RPB + f] = o[k][s2];
+      for (int s2 = 0; s2 < FF::RN; ++s2) bufa[lds_slot<L, false>(FF::out_index(t, k, s2)) * TS::NF + f] = o[k][s2];
   __syncthreads();
   if (valid) {
     C2<T>* X = fld(4);
     C2<T>* Y = fld(5);
     for (int nn = t; nn < mt; nn += TPF) {
-      const C2<T> gp = bufa[lds_slot<L, false>(nn) * RPB + f];
-      const C2<T> gm = cconj(bufa[lds_slot<L, false>((L - nn) % L) * RPB + f]);
+      const C2<T> gp = bufa[lds_slot<L, false>(nn) * TS::NF + f];
+      const C2<T> gm = cconj(bufa[lds_slot<L, false>((L - nn) % L) * TS::NF + f]);
       X[nn] = {T(0.5) * (gp.x + gm.x), T(0.5) * (gp.y + gm.y)};
       Y[nn] = {T(0.5) * (gp.y - gm.y), T(-0.5) * (gp.x - gm.x)};
     }
@@ -836,7 +800,6 @@ __attribute__((amdgpu_waves_per_eu(ZShape<T, L>::WAVES > 0 ? ZShape<T, L>::WAVES
   constexpr int NF = Z::NF, TPF = Z::TPF;
   using FF = Fft<T, L, TPF, -1, false, Z::SWZ>;
   extern __shared__ unsigned char lds_raw[];
-  C2<T>* buf = reinterpret_cast<C2<T>*>(lds_raw);
   const int tiles = (d.mt + NF - 1) / NF;
   const int ntiles = tiles * io.nfields * nplanes;
   const int f = threadIdx.x % NF, t = threadIdx.x / NF;
@@ -859,8 +822,7 @@ __attribute__((amdgpu_waves_per_eu(ZShape<T, L>::WAVES > 0 ? ZShape<T, L>::WAVES
   };
   auto transform_store = [&](int id, typename FF::In& cur) {
     typename FF::Out vo;
-    if constexpr (Z::SPLIT) FF::template run_split<NF>(cur, vo, reinterpret_cast<T*>(lds_raw), W, t, f);
-    else FF::template run<NF>(cur, vo, buf, buf, W, t, f);
+    FF::template run<NF, Z::SPLIT>(cur, vo, lds_raw, W, t, f);
     const int tile = id % tiles, rest = id / tiles;
     const int fld = rest % io.nfields, pl = rest / io.nfields;
     const int n = tile * NF + f;
@@ -1010,7 +972,7 @@ hipError_t launch_theta(tc_ctx* c, int np) {
 template <int L>
 static hipError_t run_theta_adj(tc_ctx* c, int np, void* inter) {
   using TS = TShape<double, L>;
-  const size_t lds = TS::LDS;
+  const size_t lds = TS::LDS_ADJ;
   static bool attr = false;
   if (!attr) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_theta_adj<double, L>),
