@@ -737,8 +737,6 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
   }
   std::vector<double> ltab;
   if (c->flin) {
-    // places past the last node stay zero
-    if (e == hipSuccess) e = hipMemsetAsync(c->flin, 0, c->flin_bytes, c->stream);
     ltab = line_tables(d, c->rc);
     up(c->ltab, ltab.data(), ltab.size() * sizeof(double));
   }

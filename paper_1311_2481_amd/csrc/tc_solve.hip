@@ -56,8 +56,7 @@ __device__ __forceinline__ bool make_lane(const Dims& d, ModeLane& L) {
 }
 
 // ------------------------------------------------------------------ factor
-__global__ void k_factor(const double* __restrict__ rc, double* __restrict__ fac, double* __restrict__ flin,
-                         LineShape ln, Dims d, int* bad) {
+__global__ void k_factor(const double* __restrict__ rc, double* __restrict__ fac, Dims d, int* bad) {
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= NOPS * d.ndm) return;
   const int op = gid / d.ndm, dm = gid - op * d.ndm;
@@ -82,25 +81,49 @@ __global__ void k_factor(const double* __restrict__ rc, double* __restrict__ fac
     sec[0] = E.U[0][0];
     for (int c = 1; c <= 4; ++c) sec[c] = (ip + c <= M) ? row[HW + c] : 0.0;
     for (int c = 0; c <= 4; ++c) F[(int64_t)(4 + c) * d.ndm] = sec[c];
-    if (flin) {
-      // the same in the line kernels' lane-contiguous layout
-      const int x = rev ? ln.lps * ln.rpl - 1 - j : j, k = x / ln.rpl, r = x % ln.rpl;
-      double* Lp = flin + ((int64_t)op * d.ndm + dm) * NFAC * ln.lps * ln.rpl;
-      auto put = [&](int kind, int c, double x) {
-        Lp[(int64_t)(kind * ln.rpl + r) * 4 * ln.lps + (c / 2) * 2 * ln.lps + 2 * k + c % 2] = x;
-      };
-      for (int q = 0; q < 4; ++q) put(0, q, mult[q]);
-      for (int q = 0; q < 4; ++q) put(1, q, sec[q + 1] * sec[0]);
-      Lp[(int64_t)8 * ln.rpl * ln.lps + r * ln.lps + k] = sec[0];
-    }
   }
   if (flag) atomicOr(bad, 1);
 }
 
+// The line kernels' copy of the factors (flin, see tc_internal.h): one
+// workgroup takes row r of every lane for LINE_TILE modes of one operator
+// through LDS, so that both the reads (128 bytes of consecutive modes) and
+// the writes (whole rows of a block) are contiguous.  Written from k_factor,
+// 8 bytes here and there, the copy took as long as the factorisation.
+constexpr int LINE_TILE = 16;
+__global__ __launch_bounds__(256) void k_factor_lines(const double* __restrict__ fac, double* __restrict__ flin,
+                                                      LineShape ln, Dims d) {
+  __shared__ double t[LINE_TILE * NFAC * LINE_LPS_MAX];
+  const int lps = ln.lps, rpl = ln.rpl, r = blockIdx.y, op = blockIdx.z, M = d.n_r - 1;
+  const int dm0 = blockIdx.x * LINE_TILE, count = LINE_TILE * NFAC * lps;
+  for (int i = threadIdx.x; i < count; i += blockDim.x) {
+    const int m = i % LINE_TILE, c = i / LINE_TILE % NFAC, k = i / (LINE_TILE * NFAC);
+    const int x = rpl * k + r, j = op == OP_P ? x : lps * rpl - 1 - x;
+    t[(m * NFAC + c) * lps + k] = (j <= M && dm0 + m < d.ndm) ? facp(fac, d, op, j)[(int64_t)c * d.ndm + dm0 + m] : 0.0;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < count; i += blockDim.x) {
+    const int m = i / (NFAC * lps), w = i % (NFAC * lps);
+    if (dm0 + m >= d.ndm) break;
+    double* B = flin + ((int64_t)op * d.ndm + dm0 + m) * NFAC * lps * rpl;
+    const double* v = t + m * NFAC * lps;
+    if (w < 8 * lps) {
+      const int kind = w / (4 * lps), e = w % (4 * lps), k = e % (2 * lps) / 2, c = e / (2 * lps) * 2 + e % 2;
+      B[(int64_t)(kind * rpl + r) * 4 * lps + e] = kind ? v[(5 + c) * lps + k] * v[4 * lps + k] : v[c * lps + k];
+    } else {
+      B[(int64_t)8 * rpl * lps + r * lps + (w - 8 * lps)] = v[4 * lps + (w - 8 * lps)];
+    }
+  }
+}
+
 hipError_t launch_factor(tc_ctx* c, int* bad_dev) {
   const int total = NOPS * c->d.ndm;
-  hipLaunchKernelGGL(k_factor, dim3((total + 63) / 64), dim3(64), 0, c->stream, c->rc_dev, c->fac, c->flin,
-                     line_shape(c->d), c->d, bad_dev);
+  hipLaunchKernelGGL(k_factor, dim3((total + 63) / 64), dim3(64), 0, c->stream, c->rc_dev, c->fac, c->d, bad_dev);
+  if (c->flin) {
+    const LineShape ln = line_shape(c->d);
+    hipLaunchKernelGGL(k_factor_lines, dim3((c->d.ndm + LINE_TILE - 1) / LINE_TILE, ln.rpl, NOPS), dim3(256), 0,
+                       c->stream, c->fac, c->flin, ln, c->d);
+  }
   return hipGetLastError();
 }
 
@@ -231,7 +254,10 @@ __global__ __launch_bounds__(64) void k_solve(const double* __restrict__ rc, con
 }
 
 hipError_t launch_solve(tc_ctx* c, int op, int transposed, const cd* rhs, cd* x) {
-  if (c->flin) return launch_solve_line(c, op, 1, transposed, rhs, x);
+  // one lane per mode has lanes enough from 32768 distinct modes on, and
+  // reads the rows it needs once (us, line against sweeps, forward: 28
+  // against 48 on 48 x 128 x 256, 149 against 132 on 64 x 256 x 512)
+  if (c->flin && c->d.ndm < 32768) return launch_solve_line(c, op, 1, transposed, rhs, x);
   if (transposed) return launch_solve_t(c, op, rhs, x);
   const int blocks = (c->d.ndm + 63) / 64;
   hipLaunchKernelGGL(k_solve, dim3(blocks), dim3(64), 0, c->stream, c->rc_dev, c->fac, c->d, op, rhs, x);
