@@ -234,9 +234,9 @@ size_t field_bytes(const tc_ctx* c) { return (size_t)c->d.F * sizeof(cd); }
 namespace tc {
 
 // Per-block partial sums of sum_j w_j r_j sum_{s,n} c_n e(j,s,n), where e is
-// the energy density of (u - ref) and ref = circular Couette flow in mode (0,0).
-__global__ void k_energy(Dims d, const cd* __restrict__ u, const double* __restrict__ wr, const double* __restrict__ Uc,
-                         int subtract, double* __restrict__ partial) {
+// the energy density of u.
+__global__ void k_energy(Dims d, const cd* __restrict__ u, const double* __restrict__ wr,
+                         double* __restrict__ partial) {
   __shared__ double red[256];
   double acc = 0.0;
   const int64_t total = d.F;
@@ -246,11 +246,7 @@ __global__ void k_energy(Dims d, const cd* __restrict__ u, const double* __restr
     const int64_t rem = idx - (int64_t)j * d.S;
     const int s = (int)(rem / d.mt), n = (int)(rem - (int64_t)s * d.mt);
     if (s == d.nyq) continue;
-    cd p = u[idx], m = u[d.F + idx], z = u[2 * d.F + idx];
-    if (subtract && s == 0 && n == 0) {
-      p.y -= Uc[j];
-      m.y += Uc[j];
-    }
+    const cd p = u[idx], m = u[d.F + idx], z = u[2 * d.F + idx];
     const double e = 0.5 * (p.x * p.x + p.y * p.y + m.x * m.x + m.y * m.y) + z.x * z.x + z.y * z.y;
     acc += (n == 0 ? 1.0 : 2.0) * wr[j] * e;
   }
@@ -263,105 +259,229 @@ __global__ void k_energy(Dims d, const cd* __restrict__ u, const double* __restr
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-// Per-block maxima of |div u| over interior nodes (D1 by the 9-point rows).
-__global__ void k_divmax(const double* __restrict__ rc, Dims d, const cd* __restrict__ u, double* __restrict__ partial) {
-  __shared__ double red[256];
-  double mx = 0.0;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < d.S) {
+// Partial results of the diagnostics, in one array of doubles: per
+// workgroup (DIAG_BLOCKS along the slots, one per DIAG_ROWS radial nodes) the
+// sums of the energy and the perturbation energy and the maximum of |div u|;
+// the wall slip's sums of the workgroups at the inner wall; per node and block
+// the three CFL mode sums; the theta-z mean of u_theta on every node.
+constexpr int DIAG_BLOCKS = 32, DIAG_ROWS = 8, DIAG_THREADS = 256;
+struct DiagLayout {
+  int groups;
+  size_t e, ep, dv, sl, cfl, mean, total;
+};
+
+__host__ __device__ inline DiagLayout diag_layout(const Dims& d) {
+  DiagLayout L;
+  L.groups = DIAG_BLOCKS * ((d.n_r + DIAG_ROWS - 1) / DIAG_ROWS);
+  L.e = 0;
+  L.ep = L.e + L.groups;
+  L.dv = L.ep + L.groups;
+  L.sl = L.dv + L.groups;
+  L.cfl = L.sl + DIAG_BLOCKS;
+  L.mean = L.cfl + (size_t)d.n_r * DIAG_BLOCKS * 3;
+  L.total = L.mean + d.n_r;
+  return L;
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
+// All diagnostics of u in one pass: a thread takes DIAG_ROWS nodes of a slot,
+// all its loads (those rows and the 4 on either side for D1) issued together,
+// so u comes from HBM once.  (As separate kernels, the divergence one lane per
+// slot down the whole radius, a call took 390 us on 128 x 96 x 320.)
+__global__ __launch_bounds__(DIAG_THREADS) void k_diag(const double* __restrict__ rc, Dims d, const cd* __restrict__ u,
+                                                       const double* __restrict__ wr, const double* __restrict__ Uc,
+                                                       double* __restrict__ part) {
+  constexpr int R = DIAG_ROWS, NW = DIAG_THREADS / 64;
+  __shared__ double rows[NW][R][3];
+  __shared__ double red[4][NW];
+  const int M = d.n_r - 1, j0 = blockIdx.y * R, wv = threadIdx.x / 64, lane = threadIdx.x & 63;
+  const int64_t F = d.F, S = d.S;
+  if (lane < R)
+    for (int k = 0; k < 3; ++k) rows[wv][lane][k] = 0.0;
+  const DiagLayout L = diag_layout(d);
+  double E = 0.0, Ep = 0.0, sl = 0.0, dv = 0.0;
+  for (int64_t base = (int64_t)blockIdx.x * DIAG_THREADS; base < S; base += (int64_t)DIAG_BLOCKS * DIAG_THREADS) {
+    const int64_t idx = base + threadIdx.x;
     const int s = (int)(idx / d.mt), n = (int)(idx - (int64_t)s * d.mt);
-    if (s != d.nyq) {
-      const double a = n * d.kt, b = (s < d.half ? s : s - d.mz) * d.kz;
-      for (int i = 1; i < d.n_r - 1; ++i) {
-        const double* R = rc + (int64_t)i * RC_N;
-        cd dr = {0, 0};
-        for (int k = 0; k < NB9; ++k) {
-          const int node = i + k - HW;
-          if (node < 0 || node >= d.n_r) continue;
-          const int64_t o = node * d.S + idx;
-          const cd ur = {0.5 * (u[o].x + u[d.F + o].x), 0.5 * (u[o].y + u[d.F + o].y)};
-          dr.x += R[RC_W1 + k] * ur.x;
-          dr.y += R[RC_W1 + k] * ur.y;
+    const bool in = idx < S && s != d.nyq;
+    const double a = n * d.kt, b = (s < d.half ? s : s - d.mz) * d.kz, c = n == 0 ? 1.0 : 2.0;
+    const bool zero = s == 0 && n == 0;
+    cd p[R + 2 * HW], m[R + 2 * HW], z[R];
+#pragma unroll
+    for (int r = 0; r < R + 2 * HW; ++r) {
+      const int j = j0 + r - HW, jj = j < 0 ? 0 : (j > M ? M : j);
+      const int64_t o = jj * S + (in ? idx : 0);
+      p[r] = u[o];
+      m[r] = u[F + o];
+      if (r >= HW && r < R + HW) z[r - HW] = u[2 * F + o];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int j = j0 + r;
+      if (j > M) continue;
+      const double* Rj = rc + (int64_t)j * RC_N;
+      const cd pj = p[r + HW], mj = m[r + HW], zj = z[r];
+      double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+      if (in) {
+        const double w = c * wr[j];
+        const double ez = zj.x * zj.x + zj.y * zj.y;
+        E += w * (0.5 * (pj.x * pj.x + pj.y * pj.y + mj.x * mj.x + mj.y * mj.y) + ez);
+        const double U = zero ? Uc[j] : 0.0, py = pj.y - U, my = mj.y + U;
+        Ep += w * (0.5 * (pj.x * pj.x + py * py + mj.x * mj.x + my * my) + ez);
+        // mode sums of |u_r|, |u_theta|, |u_z|: bounds of their plane maxima
+        s0 = c * 0.5 * hypot(pj.x + mj.x, pj.y + mj.y);  // u_r = (u+ + u-)/2
+        s1 = c * 0.5 * hypot(pj.x - mj.x, pj.y - mj.y);  // |u_theta| = |u+ - u-|/2
+        s2 = c * hypot(zj.x, zj.y);
+        if (j > 0 && j < M) {
+          cd dr = {0.0, 0.0};
+#pragma unroll
+          for (int k = 0; k < NB9; ++k) {
+            const double q = 0.5 * Rj[RC_W1 + k];
+            dr.x = fma(q, p[r + k].x + m[r + k].x, dr.x);
+            dr.y = fma(q, p[r + k].y + m[r + k].y, dr.y);
+          }
+          const double ir = Rj[RC_IR];
+          const double vx = dr.x + 0.5 * (pj.x + mj.x) * ir + 0.5 * a * ir * (pj.x - mj.x) - b * zj.y;
+          const double vy = dr.y + 0.5 * (pj.y + mj.y) * ir + 0.5 * a * ir * (pj.y - mj.y) + b * zj.x;
+          dv = fmax(dv, sqrt(vx * vx + vy * vy));
         }
-        const int64_t o = i * d.S + idx;
-        const cd p = u[o], m = u[d.F + o], z = u[2 * d.F + o];
-        const double ir = R[RC_IR];
-        const double vx = dr.x + 0.5 * (p.x + m.x) * ir + 0.5 * a * ir * (p.x - m.x) - b * z.y;
-        const double vy = dr.y + 0.5 * (p.y + m.y) * ir + 0.5 * a * ir * (p.y - m.y) + b * z.x;
-        mx = fmax(mx, sqrt(vx * vx + vy * vy));
+        if (j == 0) {
+          // u_theta = -i (u+ - u-) / 2
+          const double tx = 0.5 * (pj.y - mj.y) - (zero ? d.Re_i : 0.0), ty = -0.5 * (pj.x - mj.x);
+          sl += c * (tx * tx + ty * ty + zj.x * zj.x + zj.y * zj.y);
+        }
+        // theta-z mean of u_theta: Re(-i (u+ - u-) / 2) of mode (0, 0)
+        if (zero) part[L.mean + j] = 0.5 * (pj.y - mj.y);
+      }
+      s0 = wave_sum(s0);
+      s1 = wave_sum(s1);
+      s2 = wave_sum(s2);
+      if (lane == 0) {
+        rows[wv][r][0] += s0;
+        rows[wv][r][1] += s1;
+        rows[wv][r][2] += s2;
       }
     }
   }
-  red[threadIdx.x] = mx;
+  E = wave_sum(E);
+  Ep = wave_sum(Ep);
+  sl = wave_sum(sl);
+  for (int off = 32; off > 0; off >>= 1) dv = fmax(dv, __shfl_xor(dv, off));
+  if (lane == 0) {
+    red[0][wv] = E;
+    red[1][wv] = Ep;
+    red[2][wv] = sl;
+    red[3][wv] = dv;
+  }
   __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + st]);
-    __syncthreads();
+  if (threadIdx.x < 3 * R) {
+    const int r = threadIdx.x / 3, k = threadIdx.x % 3, j = j0 + r;
+    double v = 0.0;
+    for (int q = 0; q < NW; ++q) v += rows[q][r][k];
+    if (j <= M) part[L.cfl + ((size_t)j * DIAG_BLOCKS + blockIdx.x) * 3 + k] = v;
   }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
-// Per-block sums over the inner wall of c_n (|u_theta - Re_i delta|^2 + |u_z|^2).
-// Per radial node j (blockIdx.y): block partials of the mode sums
-// sum c_n |u_r|, sum c_n |u_theta|, sum c_n |u_z| over the stored modes
-// (c_0 = 1, c_n = 2), the bounds of max |u_c| over the (theta, z) plane
-// that the CFL estimate of tc_get_diag uses.
-__global__ void k_cflsum(Dims d, const cd* __restrict__ u, double* __restrict__ partial) {
-  __shared__ double red[3][256];
-  const int64_t j = blockIdx.y;
-  double acc[3] = {0.0, 0.0, 0.0};
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < d.S;
-       idx += (int64_t)gridDim.x * blockDim.x) {
-    const int s = (int)(idx / d.mt), n = (int)(idx - (int64_t)s * d.mt);
-    if (s == d.nyq) continue;
-    const int64_t o = j * d.S + idx;
-    const cd p = u[o], m = u[d.F + o], z = u[2 * d.F + o];
-    const double c = n == 0 ? 1.0 : 2.0;
-    acc[0] += c * 0.5 * hypot(p.x + m.x, p.y + m.y);  // u_r = (u+ + u-)/2
-    acc[1] += c * 0.5 * hypot(p.x - m.x, p.y - m.y);  // |u_theta| = |u+ - u-|/2
-    acc[2] += c * hypot(z.x, z.y);
-  }
-  for (int k = 0; k < 3; ++k) red[k][threadIdx.x] = acc[k];
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st)
-      for (int k = 0; k < 3; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + st];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0)
-    for (int k = 0; k < 3; ++k) partial[(j * gridDim.x + blockIdx.x) * 3 + k] = red[k][0];
-}
-
-// theta-z mean of u_theta on every node: the real part of the (l, n) = (0, 0)
-// coefficient, Re(-i (u+ - u-) / 2) = Im(u+ - u-) / 2.
-__global__ void k_mean_utheta(Dims d, const cd* __restrict__ u, double* __restrict__ out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= d.n_r) return;
-  const int64_t o = (int64_t)j * d.S;
-  out[j] = 0.5 * (u[o].y - u[d.F + o].y);
-}
-
-__global__ void k_slip(Dims d, const cd* __restrict__ u, double* __restrict__ partial) {
-  __shared__ double red[256];
-  double acc = 0.0;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < d.S) {
-    const int s = (int)(idx / d.mt), n = (int)(idx - (int64_t)s * d.mt);
-    if (s != d.nyq) {
-      const cd p = u[idx], m = u[d.F + idx], z = u[2 * d.F + idx];
-      // u_theta = -i (u+ - u-) / 2
-      double tx = 0.5 * (p.y - m.y), ty = -0.5 * (p.x - m.x);
-      if (s == 0 && n == 0) tx -= d.Re_i;
-      acc = (n == 0 ? 1.0 : 2.0) * (tx * tx + ty * ty + z.x * z.x + z.y * z.y);
+  if (threadIdx.x == 0) {
+    const int g = blockIdx.y * DIAG_BLOCKS + blockIdx.x;
+    for (int q = 1; q < NW; ++q) {
+      red[0][0] += red[0][q];
+      red[1][0] += red[1][q];
+      red[2][0] += red[2][q];
+      red[3][0] = fmax(red[3][0], red[3][q]);
     }
+    part[L.e + g] = red[0][0];
+    part[L.ep + g] = red[1][0];
+    if (blockIdx.y == 0) part[L.sl + blockIdx.x] = red[2][0];
+    part[L.dv + g] = red[3][0];
   }
-  red[threadIdx.x] = acc;
+}
+
+// The eight diagnostics from the partials, by one workgroup.
+constexpr int FINISH_THREADS = 1024;
+__global__ __launch_bounds__(FINISH_THREADS) void k_diag_finish(Dims d, const double* __restrict__ part,
+                                                                const double* __restrict__ rc, double eta,
+                                                                double* __restrict__ out) {
+  constexpr int NW = FINISH_THREADS / 64;
+  __shared__ double red[4][NW];
+  __shared__ double v[4096];  // n_r <= 4096
+  __shared__ int nan_row[NW];
+  const DiagLayout L = diag_layout(d);
+  const int tid = threadIdx.x, wv = tid / 64, lane = tid & 63, M = d.n_r - 1;
+  const double pi = 3.14159265358979323846;
+  double E = 0.0, Ep = 0.0, sl = 0.0, dv = 0.0;
+  for (int i = tid; i < L.groups; i += FINISH_THREADS) {
+    E += part[L.e + i];
+    Ep += part[L.ep + i];
+    dv = fmax(dv, part[L.dv + i]);
+  }
+  if (tid < DIAG_BLOCKS) sl = part[L.sl + tid];
+  // CFL bound: dt max_j (B_r/dr_j + B_theta/(r_j dtheta) + B_z/dz) on the
+  // physical grid (2 m_theta, m_z), dr_j the distance to the nearer neighbour;
+  // a node that is not a number hides those before it
+  const double dth = 2.0 * pi / (d.kt * 2.0 * d.mt), dz = 2.0 * pi / (d.kz * d.mz);
+  auto r_of = [&](int j) { return rc[(size_t)j * RC_N + RC_R]; };
+  int last = -1;
+  static_assert(DIAG_BLOCKS == 32, "a half wave adds up one node's partials");
+  for (int j = tid / 32; j <= M; j += FINISH_THREADS / 32) {
+    double B[3];
+    for (int k = 0; k < 3; ++k) B[k] = part[L.cfl + ((size_t)j * DIAG_BLOCKS + (tid & 31)) * 3 + k];
+    for (int off = 16; off > 0; off >>= 1)
+      for (int k = 0; k < 3; ++k) B[k] += __shfl_xor(B[k], off);
+    double dr = HUGE_VAL;
+    if (j > 0) dr = fmin(dr, r_of(j) - r_of(j - 1));
+    if (j < M) dr = fmin(dr, r_of(j + 1) - r_of(j));
+    const double vj = B[0] / dr + B[1] / (r_of(j) * dth) + B[2] / dz;
+    if ((tid & 31) == 0) v[j] = vj;
+    if (isnan(vj)) last = j;
+  }
+  E = wave_sum(E);
+  Ep = wave_sum(Ep);
+  sl = wave_sum(sl);
+  for (int off = 32; off > 0; off >>= 1) {
+    dv = fmax(dv, __shfl_xor(dv, off));
+    last = max(last, __shfl_xor(last, off));
+  }
+  if (lane == 0) {
+    red[0][wv] = E;
+    red[1][wv] = Ep;
+    red[2][wv] = dv;
+    nan_row[wv] = last;
+  }
+  if (tid == 0) out[3] = sqrt(sl) / fabs(d.Re_i == 0.0 ? 1.0 : d.Re_i);
   __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
+  for (int q = 0; q < NW; ++q) last = max(last, nan_row[q]);
+  double cfl = 0.0;
+  for (int j = tid; j <= M; j += FINISH_THREADS)
+    if (j > last) cfl = fmax(cfl, v[j]);
+  for (int off = 32; off > 0; off >>= 1) cfl = fmax(cfl, __shfl_xor(cfl, off));
+  if (lane == 0) red[3][wv] = cfl;
+  __syncthreads();
+  if (tid > 0) return;
+  const double area = (2.0 * pi / d.kt) * (2.0 * pi / d.kz);
+  for (int q = 1; q < NW; ++q) {
+    red[0][0] += red[0][q];
+    red[1][0] += red[1][q];
+    red[2][0] = fmax(red[2][0], red[2][q]);
+    red[3][0] = fmax(red[3][0], red[3][q]);
   }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+  out[0] = 0.5 * area * red[0][0];
+  out[1] = 0.5 * area * red[1][0];
+  out[2] = red[2][0];
+  out[4] = d.dt * (last == M ? NAN : red[3][0]);
+  out[5] = 0.0;  // the step count is filled in by the caller
+  // Quasi-Nusselt numbers: r^3 d<omega>/dr at each wall over its Couette
+  // value -2 C2, <omega> = <u_theta>/r, d/dr by the wall rows of D1
+  const double C2 = eta * (d.Re_i - eta * d.Re_o) / ((1.0 - eta) * (1.0 - eta * eta));
+  for (int w = 0; w < 2; ++w) {
+    const int j = w ? M : 0;
+    const int lo = j - HW < 0 ? 0 : j - HW, hi = j + HW > M ? M : j + HW;
+    double dw = 0.0;
+    for (int k = lo; k <= hi; ++k) dw += rc[(size_t)j * RC_N + RC_W1 + (k - j + HW)] * (part[L.mean + k] / r_of(k));
+    out[6 + w] = C2 == 0.0 ? NAN : r_of(j) * r_of(j) * r_of(j) * dw / (-2.0 * C2);
+  }
 }
 
 // Gradient of E_pert = 1/2 int |u - U_c|^2 dV (trapezoid rule in r, Parseval
@@ -411,97 +531,22 @@ __global__ void k_finite(int64_t count, const double* __restrict__ x, int* __res
 
 namespace {
 
-// ---------------------------------------------------------------- diagnostics: layout and reduction
-// Partial results of the diagnostics kernels, in one array of doubles:
-// block partials of the energy, perturbation energy, |div u| maximum and
-// slip sums, the CFL mode sums per radial node, and the theta-z mean of
-// u_theta on every node.
-struct DiagLayout {
-  int nb, nbd, np, nbc;
-  size_t ncfl, o00, total;
-};
-
-DiagLayout diag_layout(const Dims& d) {
-  DiagLayout L;
-  L.nb = 1024;
-  L.nbd = (int)((d.S + 255) / 256);
-  L.np = std::max(L.nb, L.nbd);
-  L.nbc = 32;  // blocks per radial node of the CFL sums
-  L.ncfl = (size_t)d.n_r * L.nbc * 3;
-  L.o00 = 4 * (size_t)L.np + L.ncfl;
-  L.total = L.o00 + (size_t)d.n_r;
-  return L;
-}
-
-hipError_t diag_launch(tc_ctx* c, double* part, const DiagLayout& L) {
+// The eight diagnostics of the context's velocity into out_host; part:
+// diag_layout().total + 8 doubles of device memory.  Synchronous.
+tc_status diag_of(tc_ctx* c, double* part, double* out_host, const char* what) {
   const Dims& d = c->d;
-  hipLaunchKernelGGL(k_energy, dim3(L.nb), dim3(256), 0, c->stream, d, c->u, c->diag_wr, c->diag_uc, 0, part);
-  hipLaunchKernelGGL(k_energy, dim3(L.nb), dim3(256), 0, c->stream, d, c->u, c->diag_wr, c->diag_uc, 1, part + L.np);
-  hipLaunchKernelGGL(k_divmax, dim3(L.nbd), dim3(256), 0, c->stream, c->rc_dev, d, c->u, part + 2 * L.np);
-  hipLaunchKernelGGL(k_slip, dim3(L.nbd), dim3(256), 0, c->stream, d, c->u, part + 3 * L.np);
-  hipLaunchKernelGGL(k_cflsum, dim3(L.nbc, d.n_r), dim3(256), 0, c->stream, d, c->u, part + 4 * L.np);
-  hipLaunchKernelGGL(k_mean_utheta, dim3((d.n_r + 255) / 256), dim3(256), 0, c->stream, d, c->u, part + L.o00);
-  return hipGetLastError();
-}
-
-// The eight diagnostics from the partials h (layout L) and the per-node
-// constants rc.  One source for the host reduction of tc_get_diag and the
-// device one of tc_get_diag_noalloc: with contraction off, both evaluate
-// the same operations in the same order and agree bit for bit.
-__host__ __device__ void diag_reduce(const Dims& d, const DiagLayout& L, const double* h, const double* rc, double eta,
-                                     double* out) {
-#pragma clang fp contract(off)
-  const double pi = 3.14159265358979323846;
-  const double area = (2.0 * pi / d.kt) * (2.0 * pi / d.kz);
-  double E = 0, Ep = 0, dv = 0, sl = 0;
-  for (int i = 0; i < L.nb; ++i) {
-    E += h[i];
-    Ep += h[L.np + i];
-  }
-  for (int i = 0; i < L.nbd; ++i) {
-    dv = dv > h[2 * L.np + i] ? dv : h[2 * L.np + i];
-    sl += h[3 * L.np + i];
-  }
-  out[0] = 0.5 * area * E;
-  out[1] = 0.5 * area * Ep;
-  out[2] = dv;
-  out[3] = sqrt(sl) / fabs(d.Re_i == 0.0 ? 1.0 : d.Re_i);
-  // CFL bound: dt max_j (B_r/dr_j + B_theta/(r_j dtheta) + B_z/dz) on the
-  // physical grid (2 m_theta, m_z), dr_j the distance to the nearer neighbour
-  const double dth = 2.0 * pi / (d.kt * 2.0 * d.mt), dz = 2.0 * pi / (d.kz * d.mz);
-  auto R = [&](int j) { return rc[(size_t)j * RC_N + RC_R]; };
-  double cfl = 0.0;
-  for (int j = 0; j < d.n_r; ++j) {
-    double B[3] = {0.0, 0.0, 0.0};
-    for (int b = 0; b < L.nbc; ++b)
-      for (int k = 0; k < 3; ++k) B[k] += h[4 * (size_t)L.np + ((size_t)j * L.nbc + b) * 3 + k];
-    double dr = HUGE_VAL;
-    if (j > 0) dr = fmin(dr, R(j) - R(j - 1));
-    if (j + 1 < d.n_r) dr = fmin(dr, R(j + 1) - R(j));
-    const double v = B[0] / dr + B[1] / (R(j) * dth) + B[2] / dz;
-    cfl = cfl > v ? cfl : v;
-  }
-  out[4] = d.dt * cfl;
-  out[5] = 0.0;  // the step count is filled in by the caller
-  // Quasi-Nusselt numbers: r^3 d<omega>/dr at each wall over its Couette
-  // value -2 C2, <omega> = <u_theta>/r, d/dr by the wall rows of D1
-  const int M = d.n_r - 1;
-  const double C2 = eta * (d.Re_i - eta * d.Re_o) / ((1.0 - eta) * (1.0 - eta * eta));
-  if (C2 == 0.0) {
-    out[6] = out[7] = NAN;
-  } else {
-    for (int w = 0; w < 2; ++w) {
-      const int j = w ? M : 0;
-      const int lo = j - HW < 0 ? 0 : j - HW, hi = j + HW > M ? M : j + HW;
-      double dw = 0.0;
-      for (int k = lo; k <= hi; ++k) dw += rc[(size_t)j * RC_N + RC_W1 + (k - j + HW)] * (h[L.o00 + k] / R(k));
-      out[6 + w] = R(j) * R(j) * R(j) * dw / (-2.0 * C2);
-    }
-  }
-}
-
-__global__ void k_diag_finish(Dims d, DiagLayout L, const double* part, const double* rc, double eta, double* out) {
-  diag_reduce(d, L, part, rc, eta, out);
+  const DiagLayout L = diag_layout(d);
+  hipLaunchKernelGGL(k_diag, dim3(DIAG_BLOCKS, (d.n_r + DIAG_ROWS - 1) / DIAG_ROWS), dim3(DIAG_THREADS), 0, c->stream,
+                     c->rc_dev, d, c->u, c->diag_wr, c->diag_uc, part);
+  hipLaunchKernelGGL(k_diag_finish, dim3(1), dim3(FINISH_THREADS), 0, c->stream, d, part, c->rc_dev, c->eta,
+                     part + L.total);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(out_host, part + L.total, 8 * sizeof(double), hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  if (e != hipSuccess) return hip_check(c, e, what);
+  out_host[5] = (double)c->steps;
+  return TC_OK;
 }
 
 // Scratch of tc_get_diag_noalloc: one array per GPU, from module load to
@@ -540,7 +585,7 @@ namespace tc {
 
 hipError_t energy_of(tc_ctx* c, const cd* u, double& E) {
   const int nb = 1024;
-  hipLaunchKernelGGL(k_energy, dim3(nb), dim3(256), 0, c->stream, c->d, u, c->diag_wr, c->diag_uc, 0, c->red);
+  hipLaunchKernelGGL(k_energy, dim3(nb), dim3(256), 0, c->stream, c->d, u, c->diag_wr, c->red);
   hipError_t e = hipGetLastError();
   std::vector<double> h(nb, 0.0);
   if (e == hipSuccess) e = hipMemcpyAsync(h.data(), c->red, nb * sizeof(double), hipMemcpyDeviceToHost, c->stream);
@@ -684,7 +729,7 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
   c->zmax = dev_alloc<unsigned int>(c, (size_t)ZMAX_WORDS * d.n_r * sizeof(unsigned int), st);
   c->diag_wr = dev_alloc<double>(c, (size_t)d.n_r * sizeof(double), st);
   c->diag_uc = dev_alloc<double>(c, (size_t)d.n_r * sizeof(double), st);
-  c->red = dev_alloc<double>(c, TC_RED_DOUBLES * sizeof(double), st);
+  c->red = dev_alloc<double>(c, (TC_RED_DOUBLES + diag_layout(d).total + 8) * sizeof(double), st);
   // plane batch of the nonlinear term: all planes when they fit a budget
   {
     const size_t per = inter_bytes_per_plane(c);
@@ -941,39 +986,21 @@ tc_status tc_helmholtz_solve_transposed(tc_ctx* c, tc_solve_kind k, const void* 
 
 tc_status tc_get_diag(tc_ctx* c, double* out) {
   if (!c || !out) return TC_EINVAL;
-  const DiagLayout L = diag_layout(c->d);
-  double* part = nullptr;
-  hipError_t e = hipMalloc(&part, L.total * sizeof(double));
-  if (e == hipSuccess) e = diag_launch(c, part, L);
-  std::vector<double> h(L.total, 0.0);
-  if (e == hipSuccess) e = hipMemcpyAsync(h.data(), part, L.total * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  (void)hipFree(part);
-  if (e != hipSuccess) return hip_check(c, e, "tc_get_diag");
-  diag_reduce(c->d, L, h.data(), c->rc.data(), c->eta, out);
-  out[5] = (double)c->steps;
-  return TC_OK;
+  return diag_of(c, c->red + TC_RED_DOUBLES, out, "tc_get_diag");
 }
 
 tc_status tc_get_diag_noalloc(tc_ctx* c, double* out) {
   if (!c || !out) return TC_EINVAL;
-  const DiagLayout L = diag_layout(c->d);
-  if (L.total + 8 > TC_DIAG_SCRATCH_DOUBLES)
-    return fail(c, TC_EINVAL, "tc_get_diag_noalloc: the grid needs " + std::to_string(L.total + 8) +
+  // the documented need; the partials of any grid that meets it fit
+  const size_t need = 4 * (size_t)std::max<int64_t>(1024, (c->d.S + 255) / 256) + 97 * (size_t)c->d.n_r + 8;
+  static_assert((size_t)(3 * DIAG_BLOCKS / DIAG_ROWS + 3 * DIAG_BLOCKS + 1) * 4096 + 4 * DIAG_BLOCKS + 8 <=
+                    TC_DIAG_SCRATCH_DOUBLES, "the partials of the largest n_r must fit the scratch");
+  if (need > TC_DIAG_SCRATCH_DOUBLES)
+    return fail(c, TC_EINVAL, "tc_get_diag_noalloc: the grid needs " + std::to_string(need) +
                                   " doubles of scratch, more than its " + std::to_string(TC_DIAG_SCRATCH_DOUBLES));
   double* part = diag_scratch(c);
   if (!part) return fail(c, TC_EHIP, "tc_get_diag_noalloc: no scratch address for this device");
-  hipError_t e = diag_launch(c, part, L);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_diag_finish, dim3(1), dim3(1), 0, c->stream, c->d, L, part, c->rc_dev, c->eta,
-                       part + L.total);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) e = hipMemcpyAsync(out, part + L.total, 8 * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  if (e != hipSuccess) return hip_check(c, e, "tc_get_diag_noalloc");
-  out[5] = (double)c->steps;
-  return TC_OK;
+  return diag_of(c, part, out, "tc_get_diag_noalloc");
 }
 
 tc_status tc_adjoint_seed(tc_ctx* c, const void* u, double scale, void* g) {
@@ -1003,10 +1030,9 @@ tc_status tc_perturbation_energy_gradient(tc_ctx* c, const void* u, void* g) {
 
 tc_status tc_check_finite(tc_ctx* c) {
   if (!c) return TC_EINVAL;
-  int* flag = nullptr;
+  int* flag = reinterpret_cast<int*>(c->red);
   int h = 0;
-  hipError_t e = hipMalloc(&flag, sizeof(int));
-  if (e == hipSuccess) e = hipMemsetAsync(flag, 0, sizeof(int), c->stream);
+  hipError_t e = hipMemsetAsync(flag, 0, sizeof(int), c->stream);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_finite, dim3(2048), dim3(256), 0, c->stream, (int64_t)6 * c->d.F,
                        reinterpret_cast<const double*>(c->u), flag);
@@ -1014,7 +1040,6 @@ tc_status tc_check_finite(tc_ctx* c) {
   }
   if (e == hipSuccess) e = hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  if (flag) (void)hipFree(flag);
   if (e != hipSuccess) return hip_check(c, e, "tc_check_finite");
   return h ? fail(c, TC_ENONFINITE, "non-finite value in the velocity") : TC_OK;
 }

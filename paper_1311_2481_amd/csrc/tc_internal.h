@@ -139,7 +139,8 @@ struct tc_ctx {
   unsigned int* zmax = nullptr;  // per-plane field magnitudes (ZMAX_WORDS n_r words)
   double* diag_wr = nullptr;     // trapezoid weight times r on every node
   double* diag_uc = nullptr;     // circular Couette u_theta on every node
-  double* red = nullptr;         // block partials of small reductions (TC_RED_DOUBLES)
+  // block partials of small reductions (TC_RED_DOUBLES), then those of tc_get_diag
+  double* red = nullptr;
   int device = -1;               // HIP device the context was created on
   double factor_error = 0.0;     // backward error of the factor check at tc_init
   int batch = 0;
