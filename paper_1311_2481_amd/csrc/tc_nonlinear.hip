@@ -242,6 +242,15 @@ template <typename T, int L> struct TShape {
   static constexpr int EU = LONG ? (F64 ? (SIXPT ? 4 : 3) : (SIXPT ? 6 : 4)) : 1;
   static constexpr int EU_ADJ = LONG ? (SIXPT ? 3 : 2) : 1;
   static constexpr int EU_CONV = L % 5 == 0 && !SIXPT ? 1 : 2;
+  // k_theta asks for its +- pairs one transform ahead, which takes at most 15
+  // more registers, the peak being in the third transform.  Below 128 points
+  // they cost a wave per SIMD (64: 17.8 -> 19.6 us on 128 x 21 x 128), as they
+  // do at 576 (8 8 3 3: 48 -> 53 us on 21 x 192 x 128); the long lengths have
+  // none to spare.  288: 272 -> 256 us on 128 x 96 x 320 and 199 -> 190 us in
+  // float, 480: 262 -> 250 and 199 -> 183 us on 64 x 160 x 320; 192: even, in
+  // float 25 -> 24 us.  (The kernels of the adjoint and of the convective form
+  // spill or lose what they would gain.)
+  static constexpr bool AHEAD = L >= 128 && L < 1024 && L != 576;
   // row and place of a thread, and its row's LDS
   static __device__ __forceinline__ int row() { return WAVE ? threadIdx.x / TPF : threadIdx.x % RPB; }
   static __device__ __forceinline__ int place() { return WAVE ? threadIdx.x % TPF : threadIdx.x / RPB; }
@@ -419,6 +428,34 @@ __device__ __forceinline__ void load_spectrum(typename F::In& v, const C2<T>* __
     }
 }
 
+// The +- pair of load_spectrum (weight m0 at n = 0) in two parts: ask() issues
+// the loads, some time before take() needs them.
+template <typename F, typename T, int L> struct PairAhead {
+  typename F::In v;
+  C2<T> b0;
+  __device__ __forceinline__ void ask(const C2<T>* __restrict__ A, const C2<T>* __restrict__ B, int mt, int t) {
+    b0 = B[0];
+#pragma unroll
+    for (int k = 0; k < F::PER0; ++k)
+#pragma unroll
+      for (int q = 0; q < F::R0; ++q) {
+        const int e = F::in_index(t, k, q), n = e <= L / 2 ? e : e - L, an = n < 0 ? -n : n;
+        v[k][q] = (n < 0 ? B : A)[an < mt ? an : 0];
+      }
+  }
+  __device__ __forceinline__ void take(int mt, bool valid, int t, T m0) {
+#pragma unroll
+    for (int k = 0; k < F::PER0; ++k)
+#pragma unroll
+      for (int q = 0; q < F::R0; ++q) {
+        const int e = F::in_index(t, k, q), n = e <= L / 2 ? e : e - L, an = n < 0 ? -n : n;
+        C2<T> x = n < 0 ? cconj(v[k][q]) : v[k][q];
+        if (q == 0 && n == 0) x = {m0 * (x.x + b0.x), m0 * (x.y - b0.y)};
+        v[k][q] = valid && an < mt && F::in_valid(t, k) ? x : C2<T>{T(0), T(0)};
+      }
+  }
+};
+
 // ------------------------------------------------------------------ theta pass
 template <typename T, int L>
 __global__ __launch_bounds__((TShape<T, L>::TPF * TShape<T, L>::RPB)) __attribute__((amdgpu_waves_per_eu(TShape<T, L>::EU)))
@@ -472,11 +509,22 @@ void k_theta(Dims d, int nplanes, C2<T>* __restrict__ inter, const C2<T>* __rest
   const T sw = ldexp(T(1), ez), isw = ldexp(T(1), -ez);
   // (g first: its two rows per element are loaded while nothing else is held)
   load_spectrum<FI, T, L, SPEC_PACKED>(v0, fld(2), fld(5), mt, valid, t, T(0), sw, T(0));
-  FI::template run<TS::NF>(v0, g, bufa, W, t, f);
-  load_spectrum<FI, T, L, SPEC_PAIR>(v0, fld(0), fld(1), mt, valid, t, T(0.5), T(0), T(0));
-  FI::template run<TS::NF>(v0, hu, bufa, W, t, f);
-  load_spectrum<FI, T, L, SPEC_PAIR>(v0, fld(3), fld(4), mt, valid, t, T(0.5), T(0), T(0));
-  FI::template run<TS::NF>(v0, hw, bufa, W, t, f);
+  if constexpr (TS::AHEAD) {
+    PairAhead<FI, T, L> pu, pw;
+    pu.ask(fld(0), fld(1), mt, t);
+    FI::template run<TS::NF>(v0, g, bufa, W, t, f);
+    pu.take(mt, valid, t, T(0.5));
+    pw.ask(fld(3), fld(4), mt, t);
+    FI::template run<TS::NF>(pu.v, hu, bufa, W, t, f);
+    pw.take(mt, valid, t, T(0.5));
+    FI::template run<TS::NF>(pw.v, hw, bufa, W, t, f);
+  } else {
+    FI::template run<TS::NF>(v0, g, bufa, W, t, f);
+    load_spectrum<FI, T, L, SPEC_PAIR>(v0, fld(0), fld(1), mt, valid, t, T(0.5), T(0), T(0));
+    FI::template run<TS::NF>(v0, hu, bufa, W, t, f);
+    load_spectrum<FI, T, L, SPEC_PAIR>(v0, fld(3), fld(4), mt, valid, t, T(0.5), T(0), T(0));
+    FI::template run<TS::NF>(v0, hw, bufa, W, t, f);
+  }
   // pointwise products (the slots hold the same points for all three)
   typename FF::In hn, nz;
 #pragma unroll
