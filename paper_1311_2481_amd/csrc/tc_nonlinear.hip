@@ -98,70 +98,85 @@ __global__ __launch_bounds__(256) void k_curl(const double* __restrict__ rc, Dim
   }
 }
 
-// The same curl with one thread per (radial node, slot) point (grid: x over
-// slots, y over nodes): each thread applies row k of D1 to the 9 rows
-// around it.  For small grids, where the marching kernel has too few lanes
-// to hide memory latency; the rows it re-reads are then cache resident.
+// The same curl with a thread for CURL_RB nodes of a slot (grid: x over slots,
+// y over groups of nodes), for grids on which the marching kernel has too few
+// lanes to hide memory latency.  The thread reads the CURL_RB + 8 rows that
+// its nodes need, without a branch between the loads, and they pass through
+// the caches three times in place of nine.  One node per thread with a branch
+// per row (which made the loads wait for one another) -> one without -> 2 ->
+// 4 -> 8 nodes, us: 101 x 48 x 96 32 -> 18 -> 18 -> 14 -> 14, 128 x 96 x 320
+// 134 -> 115 -> 86 -> 76 (4.9 TB/s of the six fields) -> 69, 128 x 160 x 320
+// 249 -> 180 -> 127 -> 116 -> 128, 32 x 16 x 32 5.7 -> 4.3 -> 4.2 -> 4.8 -> 6.7.
+constexpr int CURL_RB = 4;
 template <int KIND>
-__global__ __launch_bounds__(256) void k_curl_points(const double* __restrict__ rc, Dims d, const cd* __restrict__ u,
-                                                     cd* __restrict__ w) {
+__global__ __launch_bounds__(256) void k_curl_rows(const double* __restrict__ rc, Dims d, const cd* __restrict__ u,
+                                                   cd* __restrict__ w) {
+  constexpr int RB = CURL_RB;
   const unsigned idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (unsigned)d.S) return;
-  const int k = blockIdx.y;
+  const int j0 = blockIdx.y * RB;
   const int M = d.n_r - 1;
   const int64_t F = d.F, S = d.S;
-  const int64_t o = k * S + idx;
   const int s = (int)(idx / (unsigned)d.mt), n = (int)(idx - (unsigned)s * (unsigned)d.mt);
-  if (s == d.nyq) {
-    w[o] = cd{0, 0};
-    w[F + o] = cd{0, 0};
-    w[2 * F + o] = cd{0, 0};
-    return;
+  const bool nyq = s == d.nyq;
+  cd dp[RB], dmn[RB], dz[RB], up[RB], um[RB], uz[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) dp[i] = dmn[i] = dz[i] = up[i] = um[i] = uz[i] = cd{0, 0};
+#pragma unroll
+  for (int t = 0; t < RB + 2 * HW; ++t) {
+    // rows outside the gap count as zeros (read without a branch, which the
+    // other rows' loads would wait for)
+    const int j = j0 - HW + t;
+    const bool in = j >= 0 && j <= M;
+    const int64_t o = (in ? j : (j < 0 ? 0 : M)) * S + idx;
+    cd p = u[o], m = u[F + o], z = u[2 * F + o];
+    if (!in) p = m = z = cd{0, 0};
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      const int k = t - i;  // row j in the stencil of node j0 + i
+      if (k < 0 || k >= NB9) continue;
+      const double c = rc[(int64_t)(j0 + i <= M ? j0 + i : M) * RC_N + RC_W1 + k];
+      dp[i].x = fma(c, p.x, dp[i].x); dp[i].y = fma(c, p.y, dp[i].y);
+      dmn[i].x = fma(c, m.x, dmn[i].x); dmn[i].y = fma(c, m.y, dmn[i].y);
+      dz[i].x = fma(c, z.x, dz[i].x); dz[i].y = fma(c, z.y, dz[i].y);
+      if (KIND == 0 && k == HW) { up[i] = p; um[i] = m; uz[i] = z; }
+    }
   }
   const double a = n * d.kt;
   const double b = (s < d.half ? s : s - d.mz) * d.kz;
-  const double* R = rc + (int64_t)k * RC_N;
-  const double ir = R[RC_IR];
-  cd dp = {0, 0}, dmn = {0, 0}, dz = {0, 0};
 #pragma unroll
-  for (int t = 0; t < NB9; ++t) {
-    const int i = k - HW + t;
-    if (i < 0 || i > M) continue;
-    const double c = R[RC_W1 + t];
-    const int64_t oi = i * S + idx;
-    const cd p = u[oi], m = u[F + oi], z = u[2 * F + oi];
-    dp.x = fma(c, p.x, dp.x); dp.y = fma(c, p.y, dp.y);
-    dmn.x = fma(c, m.x, dmn.x); dmn.y = fma(c, m.y, dmn.y);
-    dz.x = fma(c, z.x, dz.x); dz.y = fma(c, z.y, dz.y);
+  for (int i = 0; i < RB; ++i) {
+    if (j0 + i > M) break;
+    cd x = dp[i], y = dmn[i], z = dz[i];
+    if constexpr (KIND == 0) {
+      const double ir = rc[(int64_t)(j0 + i) * RC_N + RC_IR];
+      // omega+ = i (a/r uz - D1 uz) - b u+ ;  omega- = i (a/r uz + D1 uz) + b u-
+      const cd tp = {a * ir * uz[i].x - dz[i].x, a * ir * uz[i].y - dz[i].y};
+      const cd tm = {a * ir * uz[i].x + dz[i].x, a * ir * uz[i].y + dz[i].y};
+      x = {-tp.y - b * up[i].x, tp.x - b * up[i].y};
+      y = {-tm.y + b * um[i].x, tm.x + b * um[i].y};
+      // omega_z = -(i/2) [ (D1 + (1+a)/r) u+ - (D1 + (1-a)/r) u- ]
+      const cd q = {dp[i].x + (1.0 + a) * ir * up[i].x - dmn[i].x - (1.0 - a) * ir * um[i].x,
+                    dp[i].y + (1.0 + a) * ir * up[i].y - dmn[i].y - (1.0 - a) * ir * um[i].y};
+      z = {0.5 * q.y, -0.5 * q.x};
+    }
+    const int64_t o = (j0 + i) * S + idx;
+    w[o] = nyq ? cd{0, 0} : x;
+    w[F + o] = nyq ? cd{0, 0} : y;
+    w[2 * F + o] = nyq ? cd{0, 0} : z;
   }
-  if constexpr (KIND == 1) {
-    w[o] = dp;
-    w[F + o] = dmn;
-    w[2 * F + o] = dz;
-    return;
-  }
-  const cd up = u[o], um = u[F + o], uz = u[2 * F + o];
-  // omega+ = i (a/r uz - D1 uz) - b u+ ;  omega- = i (a/r uz + D1 uz) + b u-
-  const cd tp = {a * ir * uz.x - dz.x, a * ir * uz.y - dz.y};
-  const cd tm = {a * ir * uz.x + dz.x, a * ir * uz.y + dz.y};
-  const cd op = {-tp.y - b * up.x, tp.x - b * up.y};
-  const cd om = {-tm.y + b * um.x, tm.x + b * um.y};
-  // omega_z = -(i/2) [ (D1 + (1+a)/r) u+ - (D1 + (1-a)/r) u- ]
-  const cd q = {dp.x + (1.0 + a) * ir * up.x - dmn.x - (1.0 - a) * ir * um.x,
-                dp.y + (1.0 + a) * ir * up.y - dmn.y - (1.0 - a) * ir * um.y};
-  w[o] = op;
-  w[F + o] = om;
-  w[2 * F + o] = cd{0.5 * q.y, -0.5 * q.x};
 }
 
 template <int KIND>
 static hipError_t run_curl(tc_ctx* c, const cd* u, cd* out) {
   const int64_t blocks = (c->d.S + 255) / 256;
   // marching lanes (one per slot) fill fewer than 2 waves per SIMD below
-  // 131072 slots per plane: use one thread per point instead
+  // 131072 slots per plane (51200, 128 nodes: 136 us against 116; above, the
+  // rows' second and third reads come from HBM: 524288, 48 nodes: 440 us
+  // against 794)
   if (c->d.S < 131072)
-    hipLaunchKernelGGL(k_curl_points<KIND>, dim3((unsigned)blocks, (unsigned)c->d.n_r), dim3(256), 0, c->stream,
-                       c->rc_dev, c->d, u, out);
+    hipLaunchKernelGGL(k_curl_rows<KIND>, dim3((unsigned)blocks, (unsigned)((c->d.n_r + CURL_RB - 1) / CURL_RB)),
+                       dim3(256), 0, c->stream, c->rc_dev, c->d, u, out);
   else
     hipLaunchKernelGGL(k_curl<KIND>, dim3((unsigned)blocks), dim3(256), 0, c->stream, c->rc_dev, c->d, u, out);
   return hipGetLastError();
