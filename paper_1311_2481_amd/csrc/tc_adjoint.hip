@@ -22,11 +22,9 @@
 // rows (tc_adjoint_pc.hip), or with each mode's radial line on chip on the
 // grids the line kernels take (tc_line.hip).  The nonlinear term's adjoint
 // follows: the transposed transforms, then the curl's adjoint below.  On
-// small grids it runs one thread per (radial node, stored mode) point, in
-// tiles of consecutive slots of one node, numbered node-fastest and walked
-// per XCD (see make_slot), and applies D1^T by gathering the (up to 9) rows
-// whose stencils touch a node; on large grids one thread per stored mode
-// sweeps the radial nodes with those rows in registers.
+// small grids a thread takes a few radial nodes of a stored mode and applies
+// D1^T to the rows whose stencils touch them; on large grids one thread per
+// stored mode sweeps the radial nodes with those rows in registers.
 #include "tc_internal.h"
 
 namespace tc {
@@ -39,66 +37,6 @@ __device__ __forceinline__ cd cimul(cd v, double w) { return cd{-w * v.y, w * v.
 __device__ __forceinline__ cd cpl(cd a, cd b) { return cd{a.x + b.x, a.y + b.y}; }
 __device__ __forceinline__ cd cmi(cd a, cd b) { return cd{a.x - b.x, a.y - b.y}; }
 
-struct Slot {
-  int k;        // radial node
-  int64_t idx;  // s * m_theta + n
-  int s, n;
-  double a, b;
-  bool nyq, zero_mode;
-};
-
-// Work tiles are (radial node k, chunk of SLOT_BLOCK slots), numbered with k
-// fastest.  The grid is 1-D with 8 ceil(ntiles / 8) workgroups and
-// workgroup b takes tile (b % 8) ceil(ntiles / 8) + b / 8: workgroups are
-// dispatched round robin over the 8 XCDs, so each XCD walks a contiguous
-// tile range, and the workgroups that need the same slots of neighbouring
-// radial planes (the +-4-row stencils) run together and share that XCD's
-// L2.  Tiles past the end belong to padding workgroups.
-constexpr int SLOT_BLOCK = 256;
-
-__host__ __device__ inline int64_t slot_tiles(const Dims& d) {
-  return (d.S + SLOT_BLOCK - 1) / SLOT_BLOCK * (int64_t)d.n_r;
-}
-
-// 32-bit index arithmetic: the tile count (at most ceil(S / 256) * 4096) and
-// the slot count S of any grid tc_init accepts are far below 2^31, and a
-// 64-bit division costs several times a 32-bit one.
-__device__ __forceinline__ bool make_slot(const Dims& d, Slot& q) {
-  const unsigned ntiles = (unsigned)slot_tiles(d);
-  const unsigned per = (ntiles + 7u) / 8u;
-  const unsigned id = (blockIdx.x % 8u) * per + blockIdx.x / 8u;
-  if (id >= ntiles) return false;
-  const unsigned nr = (unsigned)d.n_r, mt = (unsigned)d.mt;
-  q.k = (int)(id % nr);
-  const unsigned idx = (id / nr) * SLOT_BLOCK + threadIdx.x;
-  q.idx = idx;
-  if (q.idx >= d.S) return false;
-  q.s = (int)(idx / mt);
-  q.n = (int)(idx - (unsigned)q.s * mt);
-  q.a = q.n * d.kt;
-  q.b = (q.s < d.half ? q.s : q.s - d.mz) * d.kz;
-  q.nyq = q.s == d.nyq;
-  q.zero_mode = q.s == 0 && q.n == 0;
-  return true;
-}
-
-// (D^T f)_k = sum_i D[i][k] f(i) over the rows i whose stencil touches node
-// k, D = D1 (off = RC_W1) or D2 (RC_W2); f(i) is evaluated on the fly, so
-// masked or combined fields need no helper array (and no extra pass).
-template <class Fn>
-__device__ __forceinline__ cd gather_t(const double* rc, const Dims& d, int k, int off, Fn f) {
-  cd acc = cz();
-  const int M = d.n_r - 1;
-  const int lo = k - HW < 0 ? 0 : k - HW, hi = k + HW > M ? M : k + HW;
-  for (int i = lo; i <= hi; ++i) {
-    const double c = rc[(int64_t)i * RC_N + off + (k - i + HW)];
-    const cd v = f(i);
-    acc.x = fma(c, v.x, acc.x);
-    acc.y = fma(c, v.y, acc.y);
-  }
-  return acc;
-}
-
 }  // namespace
 
 // Curl adjoint: from the direct cotangents (u+d, u-d, u_zd) and those of
@@ -107,42 +45,95 @@ __device__ __forceinline__ cd gather_t(const double* rc, const Dims& d, int k, i
 //   u+  += u+d - b o+ + (i/2) (D1^T o_z + (1+a)/r o_z)
 //   u-  += u-d + b o- - (i/2) (D1^T o_z + (1-a)/r o_z)
 //   u_z += u_zd - i (a/r)(o+ + o-) + i D1^T (o+ - o-)
-__global__ void k_adj_curl(const double* __restrict__ rc, Dims d, const cd* __restrict__ nl,
-                           const cd* __restrict__ keep, cd* __restrict__ out) {
-  Slot q;
-  if (!make_slot(d, q)) return;
-  const int64_t F = d.F;
+// A thread takes ADJ_RB nodes of a slot (grid: x over slots, y over groups of
+// nodes) and reads the ADJ_RB + 8 rows of o+-, o_z whose stencils reach them
+// and its own rows of the other fields, all asked for at once; a row outside
+// the gap counts as zeros.  One node per thread and a branch for each row
+// (whose loads then waited for one another) -> two nodes, us: 32 x 16 x 32
+// 7.3 -> 4.8, 64 x 64 x 128 29 -> 26, 101 x 48 x 96 27 -> 27, 128 x 96 x 320
+// 225 -> 189 (5.0 TB/s of the fifteen fields), 128 x 160 x 320 371 -> 314.
+// Four nodes: 6.4, 25, 25, 184, 314.
+constexpr int ADJ_RB = 2;
+__global__ __launch_bounds__(256) void k_adj_curl(const double* __restrict__ rc, Dims d, const cd* __restrict__ nl,
+                                                  const cd* __restrict__ keep, cd* __restrict__ out) {
+  constexpr int RB = ADJ_RB;
+  const unsigned idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (unsigned)d.S) return;
+  const int j0 = blockIdx.y * RB;
+  const int M = d.n_r - 1;
+  const int64_t F = d.F, S = d.S;
+  const int s = (int)(idx / (unsigned)d.mt), n = (int)(idx - (unsigned)s * (unsigned)d.mt);
+  const double a = n * d.kt;
+  const double b = (s < d.half ? s : s - d.mz) * d.kz;
   const cd* upd = nl;
   const cd* umd = nl + F;
   const cd* op = nl + 2 * F;
   const cd* om = nl + 3 * F;
   const cd* uzd = nl + 4 * F;
   const cd* oz = nl + 5 * F;
-  const int k = q.k;
-  const int64_t o = k * d.S + q.idx;
-  if (q.nyq) {
-    out[o] = out[F + o] = out[2 * F + o] = cz();
-    return;
+  cd dz[RB], dd[RB], opk[RB], omk[RB], ozk[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) dz[i] = dd[i] = opk[i] = omk[i] = ozk[i] = cz();
+  // what the node's own rows add, asked for before the stencils
+  cd up[RB], um[RB], uz[RB], kp[RB], km[RB], kz[RB], ep[RB], em[RB], ez[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    const int64_t o = (j0 + i <= M ? j0 + i : M) * S + idx;
+    up[i] = upd[o];
+    um[i] = umd[o];
+    uz[i] = uzd[o];
+    kp[i] = keep[o];
+    km[i] = keep[F + o];
+    kz[i] = keep[2 * F + o];
+    ep[i] = out[o];
+    em[i] = out[F + o];
+    ez[i] = out[2 * F + o];
   }
-  const double ir = rc[(int64_t)k * RC_N + RC_IR];
-  const cd dz = gather_t(rc, d, k, RC_W1, [&](int i) { return oz[i * d.S + q.idx]; });
-  const cd dd = gather_t(rc, d, k, RC_W1, [&](int i) { return cmi(op[i * d.S + q.idx], om[i * d.S + q.idx]); });
-  const cd tz_p = cpl(dz, cs(oz[o], (1.0 + q.a) * ir));
-  const cd tz_m = cpl(dz, cs(oz[o], (1.0 - q.a) * ir));
-  const cd up = cpl(upd[o], cmi(cimul(tz_p, 0.5), cs(op[o], q.b)));
-  const cd um = cpl(umd[o], cpl(cs(om[o], q.b), cimul(tz_m, -0.5)));
-  const cd uz = cpl(uzd[o], cpl(cimul(cpl(op[o], om[o]), -q.a * ir), cimul(dd, 1.0)));
-  out[o] = cpl(out[o], cpl(up, keep[o]));
-  out[F + o] = cpl(out[F + o], cpl(um, keep[F + o]));
-  out[2 * F + o] = cpl(out[2 * F + o], cpl(uz, keep[2 * F + o]));
+#pragma unroll
+  for (int t = 0; t < RB + 2 * HW; ++t) {
+    const int j = j0 - HW + t, jj = j < 0 ? 0 : (j > M ? M : j);
+    const int64_t o = jj * S + idx;
+    cd p = op[o], m = om[o], z = oz[o];
+    if (j != jj) p = m = z = cz();
+    const cd v = cmi(p, m);
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      const int k = i - t + 2 * HW;  // node j0 + i in the stencil of row j
+      if (k < 0 || k >= NB9) continue;
+      const double c = rc[(int64_t)jj * RC_N + RC_W1 + k];
+      dz[i].x = fma(c, z.x, dz[i].x);
+      dz[i].y = fma(c, z.y, dz[i].y);
+      dd[i].x = fma(c, v.x, dd[i].x);
+      dd[i].y = fma(c, v.y, dd[i].y);
+      if (k == HW) { opk[i] = p; omk[i] = m; ozk[i] = z; }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    if (j0 + i > M) break;
+    const int64_t o = (j0 + i) * S + idx;
+    if (s == d.nyq) {
+      out[o] = out[F + o] = out[2 * F + o] = cz();
+      continue;
+    }
+    const double ir = rc[(int64_t)(j0 + i) * RC_N + RC_IR];
+    const cd tz_p = cpl(dz[i], cs(ozk[i], (1.0 + a) * ir));
+    const cd tz_m = cpl(dz[i], cs(ozk[i], (1.0 - a) * ir));
+    const cd vp = cpl(up[i], cmi(cimul(tz_p, 0.5), cs(opk[i], b)));
+    const cd vm = cpl(um[i], cpl(cs(omk[i], b), cimul(tz_m, -0.5)));
+    const cd vz = cpl(uz[i], cpl(cimul(cpl(opk[i], omk[i]), -a * ir), cimul(dd[i], 1.0)));
+    out[o] = cpl(ep[i], cpl(vp, kp[i]));
+    out[F + o] = cpl(em[i], cpl(vm, km[i]));
+    out[2 * F + o] = cpl(ez[i], cpl(vz, kz[i]));
+  }
 }
 
 // The same operation as one radial sweep per stored slot, for large grids:
 // a thread walks the nodes of its slot, keeping o+, o- and o_z of the nine
 // rows whose stencils reach the current node in registers, so every field
-// is read once (the tiled form above gathers o+-, o_z of up to nine rows
-// per point through the cache).  The stencil sums run over the rows in the
-// same order as gather_t; the two forms agree to rounding (the compiler may
+// is read once (the form above reads o+-, o_z five times through the cache).
+// The stencil sums of both run over the rows in the same order; the two forms
+// agree to rounding (the compiler may
 // fuse the remaining products and sums differently in each).
 __global__ __launch_bounds__(64) void k_adj_curl_sweep(const double* __restrict__ rc, Dims d,
                                                        const cd* __restrict__ nl, const cd* __restrict__ keep,
@@ -296,8 +287,8 @@ hipError_t adjoint_nonlinear(tc_ctx* c, const cd* u, const cd* nbar, const cd* k
     hipLaunchKernelGGL(k_adj_curl_sweep, dim3((unsigned)((d.S + 63) / 64)), dim3(64), 0, c->stream, c->rc_dev, d,
                        nl6, keep, out);
   } else {
-    const dim3 blk(SLOT_BLOCK), grd((unsigned)(8 * ((slot_tiles(d) + 7) / 8)));
-    hipLaunchKernelGGL(k_adj_curl, grd, blk, 0, c->stream, c->rc_dev, d, nl6, keep, out);
+    const dim3 grd((unsigned)((d.S + 255) / 256), (unsigned)((d.n_r + ADJ_RB - 1) / ADJ_RB));
+    hipLaunchKernelGGL(k_adj_curl, grd, dim3(256), 0, c->stream, c->rc_dev, d, nl6, keep, out);
   }
   return hipGetLastError();
 }
