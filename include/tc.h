@@ -119,8 +119,9 @@ typedef struct tc_ctx tc_ctx;
  * TC_PC_LINE=0 set at this call it uses the four-sweep kernels instead (the
  * same results up to rounding) and keeps no copy.  The curl adjoint of
  * tc_step_adjoint runs as radial sweeps on grids with at least 131072
- * stored slots per radial node and by groups of nodes elsewhere; TC_ADJ_CURL_SWEEP=1 or
- * 0 at this call picks one form on any grid (results equal up to rounding). */
+ * stored slots per radial node and by groups of nodes elsewhere;
+ * TC_ADJ_CURL_SWEEP=1 or 0 at this call picks one form on any grid (results
+ * equal up to rounding). */
 tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double dt,
                   void* hip_stream, tc_ctx** out);
 

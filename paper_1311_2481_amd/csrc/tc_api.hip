@@ -711,7 +711,7 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
   c->fac = dev_alloc<double>(c, (size_t)NOPS * d.n_r * NFAC * d.ndm * sizeof(double), st);
   // the curl adjoint as one radial sweep per slot where there are enough
   // slots for the GPU (at least 2048 waves); TC_ADJ_CURL_SWEEP=0 or 1 at
-  // this call chooses the tiled or the sweep form on any grid
+  // this call chooses the grouped or the sweep form on any grid
   {
     const char* e = std::getenv("TC_ADJ_CURL_SWEEP");
     c->adj_curl_sweep = e ? std::atoi(e) != 0 : d.S >= 131072;

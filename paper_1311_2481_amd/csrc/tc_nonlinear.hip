@@ -918,8 +918,8 @@ __attribute__((amdgpu_waves_per_eu(ZShape<T, L>::WAVES > 0 ? ZShape<T, L>::WAVES
 
 // ------------------------------------------------------------------ dispatch
 // Supported transform lengths: 2^k, 3 2^k, 9 2^k, 5 2^k and 15 2^k from 16 to
-// 2048 (radices 8, 4, 2, 3, 5), among them the paper's 320, 384, 640 and the
-// dealiased 480, 960 of its 320- and 640-point axial grids.
+// 2048 (radices 8, 4, 2, 3, 5, 6, 10), among them the paper's 320, 384, 640
+// and the dealiased 480, 960 of its 320- and 640-point axial grids.
 #define TC_FFT_LENGTHS(X)                                                                                        \
   X(16) X(24) X(32) X(40) X(48) X(64) X(80) X(96) X(120) X(128) X(144) X(160) X(192) X(240) X(256) X(288) X(320) \
   X(384) X(480) X(512) X(576) X(640) X(768) X(960) X(1024) X(1152) X(1280) X(1536) X(1920) X(2048)
