@@ -61,6 +61,14 @@ namespace tc {
 //     (200 x 64 x 128), 1350 against 1580 (256 x 96 x 320), but 5040 against
 //     2980 (160 x 256 x 512): a wave's load of one row is two slots, 32
 //     bytes, wide.
+// Grids whose waves, of 64 lanes, are at most one for each SIMD with twice
+// the lanes per slot take that many lanes of fewer rows, where it saves two
+// rows or more (one saves nothing: 31.7 against 33.0 on 48 x 32 x 64) and the
+// moves stay within 16 lanes: a wave then has 5 rows in the place of 8 to go
+// through, and there are CUs enough.  8 -> 5 rows: 34.5 -> 26.8 (32 x 16 x
+// 32), 38.6 -> 31.6 (64 x 16 x 32), 44.9 -> 40.6 (64 x 32 x 128); with two
+// waves for each SIMD 54.9 -> 78.4 (64 x 64 x 128), with 32 lanes 50.7 ->
+// 59.8 (128 x 32 x 64).
 LineShape line_shape(const Dims& d) {
   LineShape s{0, 0};
   for (int lps = 2; lps <= LINE_LPS_MAX; lps *= 2)
@@ -68,6 +76,10 @@ LineShape line_shape(const Dims& d) {
       if ((lps == 16 && d.ndm > 65536) || (lps == 32 && d.ndm >= 16384)) return s;
       s.lps = lps;
       s.rpl = std::max(HW + 1, (d.n_r + lps - 1) / lps);
+      if (lps <= 8 && (int64_t)d.ndm * 4 * lps <= 1024 * 64) {
+        const int rpl = std::max(HW + 1, (d.n_r + 2 * lps - 1) / (2 * lps));
+        if (rpl + 2 <= s.rpl) s = {2 * lps, rpl};
+      }
       break;
     }
   return s;
