@@ -252,10 +252,14 @@ template <typename T, int L> struct TShape {
   // Waves per SIMD the long kernels' registers are cut to, by the points a
   // thread holds of each spectrum (6, or 8 where the length is no multiple of
   // 6): as many as fit without a spill, or nearly (a few spilled registers
-  // cost more than the wave they buy).  0: the compiler's choice.
+  // cost more than the wave they buy).  1: the compiler's choice.  At 6 points
+  // 1536 in float spills 2 registers for its sixth wave (399 us against 415 at
+  // five on 24 x 512 x 680), 1152 and 1920 would spill 12 and 14 (389 and 824
+  // us against 334 and 736); the adjoint at 1920 spills 24 for a third wave
+  // (whole adjoint step 6.24 ms against 5.75 at two).
   static constexpr bool LONG = L >= 1024, SIXPT = L % 6 == 0, F64 = sizeof(T) == 8;
-  static constexpr int EU = LONG ? (F64 ? (SIXPT ? 4 : 3) : (SIXPT ? 6 : 4)) : 1;
-  static constexpr int EU_ADJ = LONG ? (SIXPT ? 3 : 2) : 1;
+  static constexpr int EU = LONG ? (F64 ? (SIXPT ? 4 : 3) : (SIXPT ? (L % 512 == 0 ? 6 : 5) : 4)) : 1;
+  static constexpr int EU_ADJ = LONG ? (SIXPT && L <= 1536 ? 3 : 2) : 1;
   static constexpr int EU_CONV = L % 5 == 0 && !SIXPT ? 1 : 2;
   // k_theta asks for its +- pairs one transform ahead, which takes at most 15
   // more registers, the peak being in the third transform.  Below 128 points
