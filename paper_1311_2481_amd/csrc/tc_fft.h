@@ -79,7 +79,7 @@ constexpr RadixList make_radices(int L, bool SIX = false) {
   for (; c > 0; --c) rl.r[rl.n++] = 5;
   for (; b > 0; --b) rl.r[rl.n++] = 3;
   for (; six > 0; --six) rl.r[rl.n++] = 6;
-  if (rl.r[rl.n - 1] % 3 != 0 && rl.r[0] == 8) {
+  if (rl.r[rl.n - 1] % 3 != 0 && rl.r[0] == 8 && !(rl.n == 2 && rl.r[1] == 2)) {
     for (int i = 1; i < rl.n; ++i) rl.r[i - 1] = rl.r[i];
     rl.r[rl.n - 1] = 8;
   }
@@ -207,20 +207,58 @@ template <int L, bool SWZ> __host__ __device__ constexpr int lds_len() {
   else return lds_slot<L, false>(L - 1) + 1;
 }
 
+// Mean square, over the outputs of all passes but the first (which has no
+// twiddles), of the factor by which the rounding of the one twiddle read grows
+// in the powers w^q formed from it: q by a chain of products, less where w^3
+// is read as well (w^4 = w^3 w, w^5 = w^3 w^2, w^6 = w^3 w^3, ...): level 1
+// reads it in the passes between the first and the last, whose registers have
+// room for it, level 2 in the last too (radices from 6 on).
+constexpr bool twiddle_cubed(const RadixList& rl, int pass, int level) {
+  return pass > 0 && rl.r[pass] >= 6 && level >= (pass < rl.n - 1 ? 1 : 2);
+}
+constexpr double twiddle_growth(const RadixList& rl, int level) {
+  constexpr int cubed[10] = {0, 1, 4, 1, 2, 5, 4, 5, 8, 9};
+  double sum = 0.0;
+  for (int i = 1; i < rl.n; ++i) {
+    double pass = 0.0;
+    for (int q = 1; q < rl.r[i]; ++q) pass += twiddle_cubed(rl, i, level) ? cubed[q] : q * q;
+    sum += pass / rl.r[i];
+  }
+  return sum;
+}
+
+// The plain factorisation (8s, a 4 or 2, 3s, 5s) is the measure of accuracy:
+// a list of other radices or in another order reads w^3 where its powers
+// would be worse.  (With w alone the error of omega x u, in double, was 1.57
+// times that of the plain passes at 16 points, 1.44 at 32 and 40, 1.51 at 480,
+// 1.38 at 640, 1.11 at 1152; it is 0.8 to 1.03 times at every length now, for
+// at most 7% of k_theta's time, at 288 points.)
+constexpr RadixList plain_radices(int L) {
+  RadixList rl{0, {}};
+  for (int R : {8, 4, 2, 3, 5})
+    for (; L % R == 0; L /= R) rl.r[rl.n++] = R;
+  return rl;
+}
+constexpr int twiddle_level(const RadixList& rl, const RadixList& plain) {
+  for (int level = 0; level < 2; ++level)
+    if (twiddle_growth(rl, level) <= twiddle_growth(plain, 0) + 1e-9) return level;
+  return 2;
+}
+
 // Twiddles w^q, q = 1..R-1, of one butterfly, w = W[base] (conjugated for
 // SIGN > 0).  load() reads the few that are kept, some time before apply()
 // needs them: their latency then passes during the exchange before.  In
-// double only w is read and the powers are formed one after another (w^q =
-// w^(q-1) w, a few ulp), so that only two twiddles are live: register
-// pressure decides the occupancy of the long transforms.  In float w, w^2
-// (and w^4 from radix 6 on) are read and the other powers formed by products.
-template <int R, int SIGN, typename T> struct Twiddle {
-  static constexpr bool CHAIN = sizeof(T) == 8;
-  static constexpr int N = CHAIN ? 1 : (R >= 6 ? 3 : (R == 2 || R == 3 ? 1 : 2));
+// double w is read, with CUBE w^3 too, and the other powers are formed by
+// products as they are needed, so that few twiddles are live: register
+// pressure decides the occupancy of the long transforms.  In float w, w^2 (and
+// w^4 from radix 6 on) are read and the other powers formed by products.
+template <int R, int SIGN, typename T, bool CUBE> struct Twiddle {
+  static constexpr bool F64 = sizeof(T) == 8;
+  static constexpr int N = F64 ? (CUBE ? 2 : 1) : (R >= 6 ? 3 : (R == 2 || R == 3 ? 1 : 2));
   C2<T> w[N];
   __device__ __forceinline__ void load(const C2<T>* __restrict__ W, int base) {
 #pragma unroll
-    for (int k = 0; k < N; ++k) w[k] = W[(1 << k) * base];
+    for (int k = 0; k < N; ++k) w[k] = W[(k == 0 ? 1 : F64 ? 3 : 1 << k) * base];
   }
   // v[q] *= w^q, q = 1..R-1
   __device__ __forceinline__ void apply(C2<T>* v) const {
@@ -228,7 +266,23 @@ template <int R, int SIGN, typename T> struct Twiddle {
 #pragma unroll
     for (int k = 0; k < N; ++k) u[k] = SIGN > 0 ? cconj(w[k]) : w[k];
     v[1] = cmul(v[1], u[0]);
-    if constexpr (CHAIN) {
+    if constexpr (F64 && CUBE) {
+      static_assert(R >= 6, "w^3 is a power of its own from radix 6 on");
+      C2<T> p = cmul(u[0], u[0]);
+      v[2] = cmul(v[2], p);
+      v[5] = cmul(v[5], cmul(u[1], p));
+      v[3] = cmul(v[3], u[1]);
+      v[4] = cmul(v[4], cmul(u[1], u[0]));
+      if constexpr (R >= 8) {
+        const C2<T> w6 = cmul(u[1], u[1]);
+        v[6] = cmul(v[6], w6);
+        v[7] = cmul(v[7], cmul(w6, u[0]));
+        if constexpr (R == 10) {
+          v[8] = cmul(v[8], cmul(w6, p));
+          v[9] = cmul(v[9], cmul(w6, u[1]));
+        }
+      }
+    } else if constexpr (F64) {
       C2<T> wq = u[0];
 #pragma unroll
       for (int q = 2; q < R; ++q) {
@@ -259,7 +313,8 @@ template <int R, int SIGN, typename T> struct Twiddle {
   }
 };
 
-template <typename T, int L, int TPF, int SIGN, bool REV, bool SWZ = false, bool SIX = false, bool EARLY = (L < 1024)>
+template <typename T, int L, int TPF, int SIGN, bool REV, bool SWZ = false, bool SIX = false, bool EARLY = (L < 1024),
+          int MAX_LEVEL = 2>
 struct Fft {
   static constexpr RadixList RL = REV ? reversed(make_radices(L, SIX)) : make_radices(L, SIX);
   static_assert(RL.n > 0, "unsupported transform length");
@@ -272,7 +327,10 @@ struct Fft {
   using Out = C2<T>[PERN][RN];
 
   // twiddles of one butterfly of pass PP
-  template <int PP> using Tw = Twiddle<RL.r[PP < P ? PP : P - 1], SIGN, T>;
+  static constexpr int LEVEL_BEST = twiddle_level(RL, REV ? reversed(plain_radices(L)) : plain_radices(L));
+  static constexpr int LEVEL = LEVEL_BEST < MAX_LEVEL ? LEVEL_BEST : MAX_LEVEL;
+  template <int PP>
+  using Tw = Twiddle<RL.r[PP < P ? PP : P - 1], SIGN, T, twiddle_cubed(RL, PP < P ? PP : P - 1, LEVEL)>;
 
   // twiddles of this thread's butterflies of pass PP
   template <int PP, int PER>

@@ -256,9 +256,12 @@ template <typename T, int L> struct TShape {
   // 1536 in float spills 2 registers for its sixth wave (399 us against 415 at
   // five on 24 x 512 x 680), 1152 and 1920 would spill 12 and 14 (389 and 824
   // us against 334 and 736); the adjoint at 1920 spills 24 for a third wave
-  // (whole adjoint step 6.24 ms against 5.75 at two).
+  // (whole adjoint step 6.24 ms against 5.75 at two).  The short FP64 lengths
+  // with 6 points a thread, or below 128 points, take three waves, with at most
+  // 6 registers spilled (80: 103 -> 89 us on 256 x 27 x 254; 160 would spill 11:
+  // 168 -> 183).
   static constexpr bool LONG = L >= 1024, SIXPT = L % 6 == 0, F64 = sizeof(T) == 8;
-  static constexpr int EU = LONG ? (F64 ? (SIXPT ? 4 : 3) : (SIXPT ? (L % 512 == 0 ? 6 : 5) : 4)) : 1;
+  static constexpr int EU = LONG ? (F64 ? (SIXPT ? 4 : 3) : (SIXPT ? (L % 512 == 0 ? 6 : 5) : 4)) : (F64 && (SIXPT || L < 128) ? 3 : 1);
   static constexpr int EU_ADJ = LONG ? (SIXPT && L <= 1536 ? 3 : 2) : 1;
   static constexpr int EU_CONV = L % 5 == 0 && !SIXPT ? 1 : 2;
   // k_theta asks for its +- pairs one transform ahead, which takes at most 15
@@ -616,7 +619,12 @@ void k_theta_conv(Dims d, int plane0, int nplanes, cd* __restrict__ inter, const
   // 320, but 192: 75 against 62 us on 64 x 64 x 128)
   constexpr RadixList RL = make_radices(L);
   constexpr bool EARLY = L < 1024 && RL.r[RL.n - 1] >= 6 && L % 5 != 0;
-  using FI = Fft<T, L, TPF, +1, TS::FIREV, false, false, EARLY>;
+  // the inverse transforms, under the four spectra held, read w^3 in the last
+  // pass only where there is no pass before it that could (with it 13 spilled
+  // registers at 288 points and 398 us in the place of 345 on 26 x 96 x 254; N's
+  // error without is 1.02 times that of the plain passes)
+  constexpr int TW = twiddle_growth(RL, 1) < twiddle_growth(RL, 0) ? 1 : 2;
+  using FI = Fft<T, L, TPF, +1, TS::FIREV, false, false, EARLY, TW>;
   using FF = Fft<T, L, TPF, -1, !TS::FIREV, false, false, EARLY>;
   static_assert(FI::RN == FF::R0 && FI::PERN == FF::PER0, "mirrored transforms must line up");
   extern __shared__ unsigned char lds_raw[];
