@@ -314,9 +314,10 @@ template <int R, int SIGN, typename T, bool CUBE> struct Twiddle {
 };
 
 template <typename T, int L, int TPF, int SIGN, bool REV, bool SWZ = false, bool SIX = false, bool EARLY = (L < 1024),
-          int MAX_LEVEL = 2>
+          int MAX_LEVEL = 2, bool PLAIN = false>
 struct Fft {
-  static constexpr RadixList RL = REV ? reversed(make_radices(L, SIX)) : make_radices(L, SIX);
+  static constexpr RadixList LIST = PLAIN ? plain_radices(L) : make_radices(L, SIX);
+  static constexpr RadixList RL = REV ? reversed(LIST) : LIST;
   static_assert(RL.n > 0, "unsupported transform length");
   static constexpr int P = RL.n;
   static constexpr int R0 = RL.r[0];

@@ -230,7 +230,12 @@ template <typename T, int L> struct ZShape {
   // 1536 points this took the inverse pass from 14.4 to 12.7 ms and the
   // forward pass from 7.8 to 6.4 ms on the production planes.  The float
   // kernels (94 and 73 registers) would spill under that cap.
+  // They keep to the plain radices: one butterfly of 6 or a last one of 8 more
+  // does not fit 64 registers (1920 = 8 8 5 6 spilled 13 and 37: 240 against 207
+  // us inverse, 183 against 159 forward, on 9 x 64 x 1280; 2048 = 8 8 4 8 against
+  // 8 8 8 4: 192 against 173, 162 against 134).
   static constexpr bool SPLIT = WIDE && sizeof(T) == 8;
+  template <int SIGN> using FFT = Fft<T, L, TPF, SIGN, false, SWZ, false, (L < 1024), 2, SPLIT>;
   static constexpr size_t LDS = (size_t)lds_len<L, SWZ>() * NF * (SPLIT ? sizeof(T) : sizeof(C2<T>));
   static constexpr int WAVES = SPLIT ? 8 : 0;
 };
@@ -309,7 +314,7 @@ __attribute__((amdgpu_waves_per_eu(ZShape<T, L>::WAVES > 0 ? ZShape<T, L>::WAVES
                                                                                const C2<T>* __restrict__ W) {
   using Z = ZShape<T, L>;
   constexpr int NF = Z::NF, TPF = Z::TPF;
-  using FI = Fft<T, L, TPF, +1, false, Z::SWZ>;
+  using FI = typename Z::template FFT<+1>;
   extern __shared__ unsigned char lds_raw[];
   const int tiles = (d.mt + NF - 1) / NF;
   const int ntiles = tiles * io.nfields * nplanes;
@@ -873,7 +878,7 @@ __attribute__((amdgpu_waves_per_eu(ZShape<T, L>::WAVES > 0 ? ZShape<T, L>::WAVES
                                                                                const C2<T>* __restrict__ W) {
   using Z = ZShape<T, L>;
   constexpr int NF = Z::NF, TPF = Z::TPF;
-  using FF = Fft<T, L, TPF, -1, false, Z::SWZ>;
+  using FF = typename Z::template FFT<-1>;
   extern __shared__ unsigned char lds_raw[];
   const int tiles = (d.mt + NF - 1) / NF;
   const int ntiles = tiles * io.nfields * nplanes;
