@@ -173,7 +173,13 @@ tc_status tc_helmholtz_solve_transposed(tc_ctx* ctx, tc_solve_kind k, const void
  * stored coefficient.  adj_in and adj_out must not overlap.  Rotational
  * form only (TC_EINVAL otherwise).  Its transforms run in double whatever
  * the context's precision: on a TC_FP32_BULK context it is the adjoint of
- * the FP64 step. */
+ * the FP64 step.  The first call on a context allocates work space.  Where the
+ * device has no room for it beside the context's lane-contiguous copy of the
+ * factors (tc_init), the call gives the copy up and the context runs on the
+ * four-sweep kernels from then on: the same results up to rounding, and
+ * tc_memory_bytes falls.  It never does so once work of the context that reads
+ * the copy has been captured into a graph; then, or where giving it up does
+ * not make room either, it returns TC_ENOMEM and the context is as before. */
 tc_status tc_step_adjoint(tc_ctx* ctx, const void* fwd, const void* adj_in, void* adj_out);
 
 /* Gradient of the perturbation kinetic energy E_pert(u) = 1/2 int |u - U_c|^2 dV

@@ -237,13 +237,18 @@ tc_status ensure_aux(tc_ctx* c) {
     c->aux_bytes = 0;
   }
   void* p = nullptr;
-  hipError_t e = hipMalloc(&p, need);
-  if (e != hipSuccess && c->flin) {
+  hipError_t e = no_room("adjoint") || no_room("adjoint twice") ? hipErrorOutOfMemory : hipMalloc(&p, need);
+  if (e == hipErrorOutOfMemory) {
     // no room beside the line kernels' copy of the factors: the four-sweep
-    // kernels take over
+    // kernels take over, if that makes room
     (void)hipGetLastError();
-    drop_flin(c);
-    e = hipMalloc(&p, need);
+    if (drop_flin(c)) {
+      e = no_room("adjoint twice") ? hipErrorOutOfMemory : hipMalloc(&p, need);
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        if (hipError_t el = make_flin(c); el != hipSuccess) return hip_check(c, el, "factors of the line kernels");
+      }
+    }
   }
   if (e != hipSuccess) {
     (void)hipGetLastError();

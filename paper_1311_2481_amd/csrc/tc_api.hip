@@ -28,11 +28,42 @@ tc_status hip_check(tc_ctx* c, hipError_t e, const char* what) {
   return fail(c, TC_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-void drop_flin(tc_ctx* c) {
-  (void)hipFree(c->flin);  // waits for the kernels that read it
-  c->flin = nullptr;
+bool no_room(const char* what) {
+  const char* e = std::getenv("TC_NO_ROOM");
+  return e && std::strcmp(e, what) == 0;
+}
+
+hipError_t make_flin(tc_ctx* c) {
+  const LineShape ln = line_shape(c->d);
+  const char* off = std::getenv("TC_PC_LINE");
+  if (ln.lps == 0 || (off && std::atoi(off) == 0) || no_room("lines")) return hipSuccess;
+  const size_t fac = (size_t)NOPS * ln.lps * ln.rpl * NFAC * c->d.ndm;
+  const size_t bytes = (fac + (size_t)2 * ln.rpl * LINE_TAB_F * ln.lps) * sizeof(double);
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return hipSuccess;
+  }
+  c->flin = static_cast<double*>(p);
+  c->ltab = c->flin + fac;
+  c->flin_bytes = bytes;
+  c->bytes += bytes;
+  const std::vector<double> tab = line_tables(c->d, c->rc);
+  hipError_t e = hipMemcpyAsync(c->ltab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice, c->stream);
+  if (e == hipSuccess) e = launch_factor_lines(c);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // tab ends here
+  return e;
+}
+
+bool drop_flin(tc_ctx* c) {
+  if (!c->flin || c->flin_captured) return false;
+  if (hipStreamSynchronize(c->stream) != hipSuccess || hipFree(c->flin) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  c->flin = c->ltab = nullptr;
   c->bytes -= c->flin_bytes;
-  c->omega_fresh = false;
+  return true;
 }
 
 void timer_begin(tc_ctx* c, int which) {
@@ -739,21 +770,6 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
     c->batch = std::min(c->batch, d.n_r);
     c->inter = dev_alloc<void>(c, per * (size_t)c->batch, st);
   }
-  // the line predictor-corrector where the grid allows it (TC_PC_LINE=0
-  // selects the four-sweep kernels instead); allocated last, and given up
-  // where the device has no room for its copy of the factors
-  {
-    const char* e = std::getenv("TC_PC_LINE");
-    const LineShape ln = line_shape(d);
-    if (st == TC_OK && ln.lps > 0 && !(e && std::atoi(e) == 0)) {
-      const size_t fac = (size_t)NOPS * ln.lps * ln.rpl * NFAC * d.ndm;
-      c->flin_bytes = (fac + (size_t)2 * ln.rpl * LINE_TAB_F * ln.lps) * sizeof(double);
-      tc_status sl = TC_OK;
-      c->flin = dev_alloc<double>(c, c->flin_bytes, sl);
-      if (c->flin) c->ltab = c->flin + fac;
-      else c->err.clear();
-    }
-  }
   if (st != TC_OK) {
     g_init_error = c->err;
     free_ctx(c);
@@ -779,11 +795,6 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
       wr[j] *= c->r[j];
       Uc[j] = C1 * c->r[j] + C2 / c->r[j];
     }
-  }
-  std::vector<double> ltab;
-  if (c->flin) {
-    ltab = line_tables(d, c->rc);
-    up(c->ltab, ltab.data(), ltab.size() * sizeof(double));
   }
   up(c->diag_wr, wr.data(), wr.size() * sizeof(double));
   up(c->diag_uc, Uc.data(), Uc.size() * sizeof(double));
@@ -829,12 +840,7 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
     unsigned long long* worst = nullptr;
     unsigned long long hw = 0;
     const size_t tb = (size_t)d.n_r * NOPS * d.ndm * sizeof(double);
-    if (hipMalloc(&tmp, tb) != hipSuccess && c->flin) {
-      // no room beside the line kernels' copy of the factors: give that up
-      (void)hipGetLastError();
-      drop_flin(c);
-    }
-    if ((!tmp && hipMalloc(&tmp, tb) != hipSuccess) || hipMalloc(&worst, sizeof(*worst)) != hipSuccess) {
+    if (hipMalloc(&tmp, tb) != hipSuccess || hipMalloc(&worst, sizeof(*worst)) != hipSuccess) {
       (void)hipGetLastError();
       if (tmp) (void)hipFree(tmp);
       g_init_error = "hipMalloc of the factor check's work space failed";
@@ -858,6 +864,14 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
       free_ctx(c);
       return TC_ESINGULAR;
     }
+  }
+  // the line kernels' copy of the factors, where the grid allows them
+  // (TC_PC_LINE=0 selects the four-sweep kernels instead): last, and left out
+  // where the device has no room for it
+  if (hipError_t el = make_flin(c); el != hipSuccess) {
+    g_init_error = std::string("HIP error during set-up: ") + hipGetErrorString(el);
+    free_ctx(c);
+    return TC_EHIP;
   }
   // the allocation-free diagnostics' scratch address on this device
   if (hipGetDevice(&c->device) != hipSuccess || !scratch_address(c->device)) {

@@ -120,6 +120,7 @@ struct tc_ctx {
   double* fac = nullptr;
   double* flin = nullptr;    // lane-contiguous copy of fac (line predictor-corrector only)
   size_t flin_bytes = 0;
+  bool flin_captured = false;  // a captured graph may hold its address
   double* ltab = nullptr;    // per-row tables of the line kernels (behind flin)
   bool adj_curl_sweep = false;  // curl adjoint as radial sweeps (large grids; see tc_init)
   tc::cd* tw_t = nullptr;   // exp(-2 pi i e / p_theta)
@@ -159,7 +160,6 @@ tc_status fail(tc_ctx* c, tc_status s, const std::string& msg);
 tc_status hip_check(tc_ctx* c, hipError_t e, const char* what);
 
 // launchers (return hipError_t from hipGetLastError)
-// (also fills c->flin when it is allocated)
 hipError_t launch_factor(tc_ctx* c, int* bad_dev);
 // componentwise backward error of the stored factors on one solve per
 // operator and mode (tmp: n_r * 4 * ndm doubles of work space)
@@ -226,8 +226,19 @@ size_t inter_bytes_per_plane(const tc_ctx* c);
 // kinetic energy 1/2 int |u|^2 dV of a velocity (synchronous; uses ctx->red)
 hipError_t energy_of(tc_ctx* c, const cd* u, double& E);
 
-// gives up the line kernels' copy of the factors
-void drop_flin(tc_ctx* c);
+// The line kernels' copy of the factors and their tables: make_flin allocates
+// and fills them from fac (without room for them, or where the kernels do not
+// run, it leaves c->flin NULL), drop_flin gives them up.  drop_flin refuses
+// (false) where a captured graph may hold their address, as free memory would
+// be read at its next launch, and where there is nothing to give up.
+hipError_t make_flin(tc_ctx* c);
+bool drop_flin(tc_ctx* c);
+// fills c->flin's factors from fac
+hipError_t launch_factor_lines(tc_ctx* c);
+
+// Whether the environment variable TC_NO_ROOM names this allocation, which
+// then counts as failed for want of memory (tests).
+bool no_room(const char* what);
 
 // timing helpers (no-ops unless ctx->timing)
 void timer_begin(tc_ctx* c, int which);

@@ -112,6 +112,11 @@ std::vector<double> line_tables(const Dims& d, const std::vector<double>& rc) {
 }
 
 static hipError_t run_line(tc_ctx* c, const LineArgs& x) {
+  if (!c->flin_captured) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &s) != hipSuccess) (void)hipGetLastError();
+    c->flin_captured = s != hipStreamCaptureStatusNone;
+  }
   switch (line_shape(c->d).lps) {
     case 2: return run_line_2(c, x);
     case 4: return run_line_4(c, x);

@@ -119,11 +119,13 @@ __global__ __launch_bounds__(256) void k_factor_lines(const double* __restrict__
 hipError_t launch_factor(tc_ctx* c, int* bad_dev) {
   const int total = NOPS * c->d.ndm;
   hipLaunchKernelGGL(k_factor, dim3((total + 63) / 64), dim3(64), 0, c->stream, c->rc_dev, c->fac, c->d, bad_dev);
-  if (c->flin) {
-    const LineShape ln = line_shape(c->d);
-    hipLaunchKernelGGL(k_factor_lines, dim3((c->d.ndm + LINE_TILE - 1) / LINE_TILE, ln.rpl, NOPS), dim3(256), 0,
-                       c->stream, c->fac, c->flin, ln, c->d);
-  }
+  return hipGetLastError();
+}
+
+hipError_t launch_factor_lines(tc_ctx* c) {
+  const LineShape ln = line_shape(c->d);
+  hipLaunchKernelGGL(k_factor_lines, dim3((c->d.ndm + LINE_TILE - 1) / LINE_TILE, ln.rpl, NOPS), dim3(256), 0,
+                     c->stream, c->fac, c->flin, ln, c->d);
   return hipGetLastError();
 }
 
