@@ -333,6 +333,7 @@ __global__ __launch_bounds__(DIAG_THREADS) void k_diag(const double* __restrict_
   const int64_t F = d.F, S = d.S;
   if (lane < R)
     for (int k = 0; k < 3; ++k) rows[wv][lane][k] = 0.0;
+  __syncthreads();  // lane 0 adds to what other lanes cleared
   const DiagLayout L = diag_layout(d);
   double E = 0.0, Ep = 0.0, sl = 0.0, dv = 0.0;
   for (int64_t base = (int64_t)blockIdx.x * DIAG_THREADS; base < S; base += (int64_t)DIAG_BLOCKS * DIAG_THREADS) {
