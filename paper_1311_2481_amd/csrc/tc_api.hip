@@ -291,25 +291,33 @@ __global__ void k_energy(Dims d, const cd* __restrict__ u, const double* __restr
 }
 
 // Partial results of the diagnostics, in one array of doubles: per
-// workgroup (DIAG_BLOCKS along the slots, one per DIAG_ROWS radial nodes) the
+// workgroup (blocks along the slots, one per DIAG_ROWS radial nodes) the
 // sums of the energy and the perturbation energy and the maximum of |div u|;
 // the wall slip's sums of the workgroups at the inner wall; per node and block
 // the three CFL mode sums; the theta-z mean of u_theta on every node.
-constexpr int DIAG_BLOCKS = 32, DIAG_ROWS = 8, DIAG_THREADS = 256;
+// 32 blocks, doubled while they leave slots for a second round and the
+// workgroups are fewer than 1024 (four for each CU): with 32 throughout, 9 x 512
+// x 1024 ran on 64 workgroups and took 640 us, 113 now.  The partials are then
+// those of fewer than 2 DIAG_GROUPS workgroups, with 32 blocks 109 n_r doubles
+// at most.
+constexpr int DIAG_BLOCKS = 32, DIAG_ROWS = 8, DIAG_THREADS = 256, DIAG_GROUPS = 1024;
 struct DiagLayout {
-  int groups;
+  int blocks, groups;
   size_t e, ep, dv, sl, cfl, mean, total;
 };
 
 __host__ __device__ inline DiagLayout diag_layout(const Dims& d) {
   DiagLayout L;
-  L.groups = DIAG_BLOCKS * ((d.n_r + DIAG_ROWS - 1) / DIAG_ROWS);
+  const int rows = (d.n_r + DIAG_ROWS - 1) / DIAG_ROWS;
+  L.blocks = DIAG_BLOCKS;
+  while ((int64_t)L.blocks * DIAG_THREADS < d.S && L.blocks * rows < DIAG_GROUPS) L.blocks *= 2;
+  L.groups = L.blocks * rows;
   L.e = 0;
   L.ep = L.e + L.groups;
   L.dv = L.ep + L.groups;
   L.sl = L.dv + L.groups;
-  L.cfl = L.sl + DIAG_BLOCKS;
-  L.mean = L.cfl + (size_t)d.n_r * DIAG_BLOCKS * 3;
+  L.cfl = L.sl + L.blocks;
+  L.mean = L.cfl + (size_t)d.n_r * L.blocks * 3;
   L.total = L.mean + d.n_r;
   return L;
 }
@@ -336,7 +344,7 @@ __global__ __launch_bounds__(DIAG_THREADS) void k_diag(const double* __restrict_
   __syncthreads();  // lane 0 adds to what other lanes cleared
   const DiagLayout L = diag_layout(d);
   double E = 0.0, Ep = 0.0, sl = 0.0, dv = 0.0;
-  for (int64_t base = (int64_t)blockIdx.x * DIAG_THREADS; base < S; base += (int64_t)DIAG_BLOCKS * DIAG_THREADS) {
+  for (int64_t base = (int64_t)blockIdx.x * DIAG_THREADS; base < S; base += (int64_t)L.blocks * DIAG_THREADS) {
     const int64_t idx = base + threadIdx.x;
     const int s = (int)(idx / d.mt), n = (int)(idx - (int64_t)s * d.mt);
     const bool in = idx < S && s != d.nyq;
@@ -414,10 +422,10 @@ __global__ __launch_bounds__(DIAG_THREADS) void k_diag(const double* __restrict_
     const int r = threadIdx.x / 3, k = threadIdx.x % 3, j = j0 + r;
     double v = 0.0;
     for (int q = 0; q < NW; ++q) v += rows[q][r][k];
-    if (j <= M) part[L.cfl + ((size_t)j * DIAG_BLOCKS + blockIdx.x) * 3 + k] = v;
+    if (j <= M) part[L.cfl + ((size_t)j * L.blocks + blockIdx.x) * 3 + k] = v;
   }
   if (threadIdx.x == 0) {
-    const int g = blockIdx.y * DIAG_BLOCKS + blockIdx.x;
+    const int g = blockIdx.y * L.blocks + blockIdx.x;
     for (int q = 1; q < NW; ++q) {
       red[0][0] += red[0][q];
       red[1][0] += red[1][q];
@@ -449,17 +457,18 @@ __global__ __launch_bounds__(FINISH_THREADS) void k_diag_finish(Dims d, const do
     Ep += part[L.ep + i];
     dv = fmax(dv, part[L.dv + i]);
   }
-  if (tid < DIAG_BLOCKS) sl = part[L.sl + tid];
+  for (int i = tid; i < L.blocks && wv == 0; i += 64) sl += part[L.sl + i];
   // CFL bound: dt max_j (B_r/dr_j + B_theta/(r_j dtheta) + B_z/dz) on the
   // physical grid (2 m_theta, m_z), dr_j the distance to the nearer neighbour;
   // a node that is not a number hides those before it
   const double dth = 2.0 * pi / (d.kt * 2.0 * d.mt), dz = 2.0 * pi / (d.kz * d.mz);
   auto r_of = [&](int j) { return rc[(size_t)j * RC_N + RC_R]; };
   int last = -1;
-  static_assert(DIAG_BLOCKS == 32, "a half wave adds up one node's partials");
+  static_assert(DIAG_BLOCKS % 32 == 0, "a half wave adds up one node's partials");
   for (int j = tid / 32; j <= M; j += FINISH_THREADS / 32) {
-    double B[3];
-    for (int k = 0; k < 3; ++k) B[k] = part[L.cfl + ((size_t)j * DIAG_BLOCKS + (tid & 31)) * 3 + k];
+    double B[3] = {0.0, 0.0, 0.0};
+    for (int q = tid & 31; q < L.blocks; q += 32)
+      for (int k = 0; k < 3; ++k) B[k] += part[L.cfl + ((size_t)j * L.blocks + q) * 3 + k];
     for (int off = 16; off > 0; off >>= 1)
       for (int k = 0; k < 3; ++k) B[k] += __shfl_xor(B[k], off);
     double dr = HUGE_VAL;
@@ -568,7 +577,7 @@ namespace {
 tc_status diag_of(tc_ctx* c, double* part, double* out_host, const char* what) {
   const Dims& d = c->d;
   const DiagLayout L = diag_layout(d);
-  hipLaunchKernelGGL(k_diag, dim3(DIAG_BLOCKS, (d.n_r + DIAG_ROWS - 1) / DIAG_ROWS), dim3(DIAG_THREADS), 0, c->stream,
+  hipLaunchKernelGGL(k_diag, dim3(L.blocks, (d.n_r + DIAG_ROWS - 1) / DIAG_ROWS), dim3(DIAG_THREADS), 0, c->stream,
                      c->rc_dev, d, c->u, c->diag_wr, c->diag_uc, part);
   hipLaunchKernelGGL(k_diag_finish, dim3(1), dim3(FINISH_THREADS), 0, c->stream, d, part, c->rc_dev, c->eta,
                      part + L.total);
@@ -1006,10 +1015,12 @@ tc_status tc_get_diag(tc_ctx* c, double* out) {
 
 tc_status tc_get_diag_noalloc(tc_ctx* c, double* out) {
   if (!c || !out) return TC_EINVAL;
-  // the documented need; the partials of any grid that meets it fit
+  // the documented limit; the partials of any grid within it fit
   const size_t need = 4 * (size_t)std::max<int64_t>(1024, (c->d.S + 255) / 256) + 97 * (size_t)c->d.n_r + 8;
   static_assert((size_t)(3 * DIAG_BLOCKS / DIAG_ROWS + 3 * DIAG_BLOCKS + 1) * 4096 + 4 * DIAG_BLOCKS + 8 <=
                     TC_DIAG_SCRATCH_DOUBLES, "the partials of the largest n_r must fit the scratch");
+  static_assert((size_t)2 * DIAG_GROUPS * (3 + 1 + 3 * DIAG_ROWS + DIAG_ROWS) + 8 <= TC_DIAG_SCRATCH_DOUBLES,
+                "the partials of the most workgroups must fit the scratch");
   if (need > TC_DIAG_SCRATCH_DOUBLES)
     return fail(c, TC_EINVAL, "tc_get_diag_noalloc: the grid needs " + std::to_string(need) +
                                   " doubles of scratch, more than its " + std::to_string(TC_DIAG_SCRATCH_DOUBLES));

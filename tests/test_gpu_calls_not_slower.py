@@ -1,0 +1,42 @@
+"""Calls that a change of kernel or route had made slower, each against another
+call of the same library that does comparable work on the same grid, in one
+process.  The comments give the ratio that was measured when it was slow."""
+import time
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def timed(f, repeats=5):
+    """Seconds of a call, the least of several runs of at least 5 ms."""
+    import torch
+    f()
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    f()
+    torch.cuda.synchronize()
+    n = max(3, int(5e-3 / max(time.perf_counter() - t, 1e-6)))
+    best = float("inf")
+    for _ in range(repeats):
+        t = time.perf_counter()
+        for _ in range(n):
+            f()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t) / n)
+    return best
+
+
+def solver(n_r, m_theta, m_z):
+    from paper_1311_2481_amd import Solver
+    return Solver(n_r, m_theta, m_z, 0.5, 1000.0, 0.0, 1e-9)
+
+
+@pytest.mark.parametrize("n_r,m_theta,m_z", [(9, 512, 1024), (10, 600, 1200)])
+def test_diagnostics_of_large_planes(n_r, m_theta, m_z):
+    # against the finite check, which reads the same velocity: 12.2 and 10.5 times its time
+    S = solver(n_r, m_theta, m_z)
+    d, f = timed(S.diag), timed(S.check_finite)
+    print(f"{n_r} x {m_theta} x {m_z}: diagnostics {d * 1e6:.0f} us, finite check {f * 1e6:.0f} us")
+    S.close()
+    assert d <= 8 * f
