@@ -255,11 +255,27 @@ __global__ __launch_bounds__(64) void k_solve(const double* __restrict__ rc, con
   }
 }
 
+// Whether a solve on its own takes the line kernel.  The sweeps, one lane per
+// mode, read whole cache lines, and each element once; from some number of
+// modes on they have lanes enough too (us, line against sweeps).  Forward, at 32768 distinct modes: 28 against 48 on 48 x 128
+// x 256, 149 against 132 on 64 x 256 x 512; earlier where the 16 lanes have more
+// than an eighth of their rows empty, 73 against 66 on 66 x 128 x 380 (but 75
+// against 86 on 80 x 128 x 380).  Transposed, whose sweeps load eight rows at a
+// time, by the modes times the rows a lane has for each node: 37 against 42 on
+// 64 x 100 x 326, 52 against 48 on 64 x 128 x 380; with 32 lanes, 88 against 106
+// on 200 x 96 x 170, 79 against 70 on 129 x 96 x 170, 164 against 87 on 129 x 100
+// x 320.
+static bool solve_on_lines(const tc_ctx* c, int transposed) {
+  if (!c->flin) return false;
+  const LineShape ln = line_shape(c->d);
+  const int64_t places = (int64_t)ln.lps * ln.rpl, n_r = c->d.n_r, ndm = c->d.ndm;
+  if (transposed) return ndm * places < (ln.lps == 32 ? 9216 : 16384) * n_r;
+  if (ln.lps == 16 && places * 8 > n_r * 9) return ndm < 20480;
+  return ndm < 32768;
+}
+
 hipError_t launch_solve(tc_ctx* c, int op, int transposed, const cd* rhs, cd* x) {
-  // one lane per mode has lanes enough from 32768 distinct modes on, and
-  // reads the rows it needs once (us, line against sweeps, forward: 28
-  // against 48 on 48 x 128 x 256, 149 against 132 on 64 x 256 x 512)
-  if (c->flin && c->d.ndm < 32768) return launch_solve_line(c, op, 1, transposed, rhs, x);
+  if (solve_on_lines(c, transposed)) return launch_solve_line(c, op, 1, transposed, rhs, x);
   if (transposed) return launch_solve_t(c, op, rhs, x);
   const int blocks = (c->d.ndm + 63) / 64;
   hipLaunchKernelGGL(k_solve, dim3(blocks), dim3(64), 0, c->stream, c->rc_dev, c->fac, c->d, op, rhs, x);

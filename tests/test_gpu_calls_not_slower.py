@@ -32,6 +32,25 @@ def solver(n_r, m_theta, m_z):
     return Solver(n_r, m_theta, m_z, 0.5, 1000.0, 0.0, 1e-9)
 
 
+@pytest.mark.parametrize("n_r,m_theta,m_z,transposed", [(129, 100, 320, True), (200, 100, 300, True),
+                                                        (100, 128, 380, True), (66, 128, 380, False)])
+def test_solves_against_the_sweeps(n_r, m_theta, m_z, transposed, monkeypatch):
+    # against the kernels of a context without the line copy: 1.85, 1.42, 1.29 and 1.10 times
+    import torch
+    t = []
+    for line in ("1", "0"):
+        monkeypatch.setenv("TC_PC_LINE", line)
+        S = solver(n_r, m_theta, m_z)
+        f = S.empty(1).fill_(complex(1.0, 0.5))
+        x = S.empty(1)
+        t.append([timed(lambda: S.solve(k, f, out=x, transposed=transposed)) for k in ("P", "Uz")])
+        S.close()
+        torch.cuda.synchronize()
+    for k, a, b in zip(("P", "Uz"), *t):
+        print(f"{n_r} x {m_theta} x {m_z} {k} transposed={transposed}: {a * 1e6:.0f} us, sweeps {b * 1e6:.0f} us")
+        assert a <= 1.06 * b
+
+
 @pytest.mark.parametrize("n_r,m_theta,m_z", [(9, 512, 1024), (10, 600, 1200)])
 def test_diagnostics_of_large_planes(n_r, m_theta, m_z):
     # against the finite check, which reads the same velocity: 12.2 and 10.5 times its time
