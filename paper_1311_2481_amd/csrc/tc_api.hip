@@ -825,14 +825,14 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
   if (e == hipSuccess) e = hipMemsetAsync(c->N_cur, 0, 3 * FB, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->p, 0, FB, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->zmax, 0, (size_t)ZMAX_WORDS * d.n_r * sizeof(unsigned int), c->stream);
-  int* bad = nullptr;
-  if (e == hipSuccess) e = hipMalloc(&bad, sizeof(int));
+  // (the factorisation's flag and the check's result and work space lie in
+  // buffers that hold nothing yet: the check needs a field's size)
+  int* const bad = reinterpret_cast<int*>(c->red);
   if (e == hipSuccess) e = hipMemsetAsync(bad, 0, sizeof(int), c->stream);
   if (e == hipSuccess) e = launch_factor(c, bad);
   int hbad = 0;
   if (e == hipSuccess) e = hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  if (bad) (void)hipFree(bad);
   if (e != hipSuccess) {
     g_init_error = std::string("HIP error during set-up: ") + hipGetErrorString(e);
     free_ctx(c);
@@ -846,23 +846,13 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
   // the factors are unpivoted: check their backward error on one solve per
   // operator and mode before accepting them
   {
-    double* tmp = nullptr;
-    unsigned long long* worst = nullptr;
+    unsigned long long* const worst = reinterpret_cast<unsigned long long*>(c->red);
     unsigned long long hw = 0;
-    const size_t tb = (size_t)d.n_r * NOPS * d.ndm * sizeof(double);
-    if (hipMalloc(&tmp, tb) != hipSuccess || hipMalloc(&worst, sizeof(*worst)) != hipSuccess) {
-      (void)hipGetLastError();
-      if (tmp) (void)hipFree(tmp);
-      g_init_error = "hipMalloc of the factor check's work space failed";
-      free_ctx(c);
-      return TC_ENOMEM;
-    }
+    static_assert(NOPS * sizeof(double) <= 2 * sizeof(cd), "the check's work space fits one field of m_z = 2 |l| slots");
     e = hipMemsetAsync(worst, 0, sizeof(*worst), c->stream);
-    if (e == hipSuccess) e = launch_factor_check(c, tmp, worst);
+    if (e == hipSuccess) e = launch_factor_check(c, reinterpret_cast<double*>(c->omega), worst);
     if (e == hipSuccess) e = hipMemcpyAsync(&hw, worst, sizeof(hw), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(tmp);
-    (void)hipFree(worst);
     if (e != hipSuccess) {
       g_init_error = std::string("HIP error during the factor check: ") + hipGetErrorString(e);
       free_ctx(c);

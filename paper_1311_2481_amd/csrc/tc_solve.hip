@@ -86,33 +86,42 @@ __global__ void k_factor(const double* __restrict__ rc, double* __restrict__ fac
 }
 
 // The line kernels' copy of the factors (flin, see tc_internal.h): one
-// workgroup takes row r of every lane for LINE_TILE modes of one operator
-// through LDS, so that both the reads (128 bytes of consecutive modes) and
-// the writes (whole rows of a block) are contiguous.  Written from k_factor,
-// 8 bytes here and there, the copy took as long as the factorisation.
-constexpr int LINE_TILE = 16;
+// workgroup takes LINE_PLACES / lps rows of every lane for LINE_TILE modes of one
+// operator through LDS, so that both the reads (128 bytes of consecutive modes)
+// and the writes (some 256 doubles of a block on end) are contiguous.  Written
+// from k_factor, 8 bytes here and there, the copy took as long as the
+// factorisation; with one row of every lane in a workgroup, whatever lps,
+// and 16-way conflicts on the writes to LDS, 1710 us on 16 x 512 x 1024 and 490
+// on 129 x 100 x 320, half of what tc_init spent on the GPU; 670 (3.6 TB/s) and
+// 360 now.
+constexpr int LINE_TILE = 16, LINE_PLACES = LINE_LPS_MAX;
 __global__ __launch_bounds__(256) void k_factor_lines(const double* __restrict__ fac, double* __restrict__ flin,
                                                       LineShape ln, Dims d) {
-  __shared__ double t[LINE_TILE * NFAC * LINE_LPS_MAX];
-  const int lps = ln.lps, rpl = ln.rpl, r = blockIdx.y, op = blockIdx.z, M = d.n_r - 1;
-  const int dm0 = blockIdx.x * LINE_TILE, count = LINE_TILE * NFAC * lps;
-  for (int i = threadIdx.x; i < count; i += blockDim.x) {
-    const int m = i % LINE_TILE, c = i / LINE_TILE % NFAC, k = i / (LINE_TILE * NFAC);
-    const int x = rpl * k + r, j = op == OP_P ? x : lps * rpl - 1 - x;
-    t[(m * NFAC + c) * lps + k] = (j <= M && dm0 + m < d.ndm) ? facp(fac, d, op, j)[(int64_t)c * d.ndm + dm0 + m] : 0.0;
+  constexpr int STRIDE = NFAC * LINE_PLACES + 1;  // doubles of a mode
+  __shared__ double t[LINE_TILE * STRIDE];
+  const int lps = ln.lps, rpl = ln.rpl, op = blockIdx.z, M = d.n_r - 1;
+  const int rows = LINE_PLACES / lps, r0 = blockIdx.y * rows, nr = rpl - r0 < rows ? rpl - r0 : rows;
+  const int dm0 = blockIdx.x * LINE_TILE, dm = dm0 + (int)threadIdx.x % LINE_TILE;
+  // row r0 + p / lps of lane p % lps
+  for (int i = threadIdx.x / LINE_TILE; i < NFAC * nr * lps; i += blockDim.x / LINE_TILE) {
+    const int c = i % NFAC, p = i / NFAC;
+    const int x = rpl * (p % lps) + r0 + p / lps, j = op == OP_P ? x : lps * rpl - 1 - x;
+    t[(threadIdx.x % LINE_TILE) * STRIDE + c * LINE_PLACES + p] =
+        (j <= M && dm < d.ndm) ? facp(fac, d, op, j)[(int64_t)c * d.ndm + dm] : 0.0;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < count; i += blockDim.x) {
-    const int m = i / (NFAC * lps), w = i % (NFAC * lps);
-    if (dm0 + m >= d.ndm) break;
+  // the three parts of a block: both kinds of coefficients, the inverse pivots
+  const int n4 = 4 * lps * nr, n1 = lps * nr;
+  for (int m = threadIdx.x / 64; m < LINE_TILE && dm0 + m < d.ndm; m += blockDim.x / 64) {
     double* B = flin + ((int64_t)op * d.ndm + dm0 + m) * NFAC * lps * rpl;
-    const double* v = t + m * NFAC * lps;
-    if (w < 8 * lps) {
-      const int kind = w / (4 * lps), e = w % (4 * lps), k = e % (2 * lps) / 2, c = e / (2 * lps) * 2 + e % 2;
-      B[(int64_t)(kind * rpl + r) * 4 * lps + e] = kind ? v[(5 + c) * lps + k] * v[4 * lps + k] : v[c * lps + k];
-    } else {
-      B[(int64_t)8 * rpl * lps + r * lps + (w - 8 * lps)] = v[4 * lps + (w - 8 * lps)];
+    const double* v = t + m * STRIDE;
+    for (int w = threadIdx.x % 64; w < n4; w += 64) {
+      const int e = w % (4 * lps), p = w / (4 * lps) * lps + e % (2 * lps) / 2, c = e / (2 * lps) * 2 + e % 2;
+      const int64_t at = (int64_t)r0 * 4 * lps + w;
+      B[at] = v[c * LINE_PLACES + p];
+      B[(int64_t)rpl * 4 * lps + at] = v[(5 + c) * LINE_PLACES + p] * v[4 * LINE_PLACES + p];
     }
+    for (int p = threadIdx.x % 64; p < n1; p += 64) B[(int64_t)8 * rpl * lps + r0 * lps + p] = v[4 * LINE_PLACES + p];
   }
 }
 
@@ -124,7 +133,8 @@ hipError_t launch_factor(tc_ctx* c, int* bad_dev) {
 
 hipError_t launch_factor_lines(tc_ctx* c) {
   const LineShape ln = line_shape(c->d);
-  hipLaunchKernelGGL(k_factor_lines, dim3((c->d.ndm + LINE_TILE - 1) / LINE_TILE, ln.rpl, NOPS), dim3(256), 0,
+  const int rows = LINE_PLACES / ln.lps;
+  hipLaunchKernelGGL(k_factor_lines, dim3((c->d.ndm + LINE_TILE - 1) / LINE_TILE, (ln.rpl + rows - 1) / rows, NOPS), dim3(256), 0,
                      c->stream, c->fac, c->flin, ln, c->d);
   return hipGetLastError();
 }
@@ -138,6 +148,14 @@ hipError_t launch_factor_lines(tc_ctx* c) {
 // the largest error over all lanes, as the bits of a non-negative double.
 __global__ void k_factor_check(const double* __restrict__ rc, const double* __restrict__ fac, Dims d,
                                double* __restrict__ tmp, unsigned long long* worst) {
+  // x0, formed once for the workgroup (formed where it is used, the sines took a
+  // quarter to half of the kernel: 738 -> 530 us on 16 x 512 x 1024, 980 -> 475 on
+  // 129 x 100 x 320)
+  extern __shared__ double x0s[];
+  const int M = d.n_r - 1;
+  for (int j = threadIdx.x; j <= M; j += blockDim.x) x0s[j] = 1.0 + 0.5 * sin(0.7 * j);
+  __syncthreads();
+  auto x0 = [&](int j) { return x0s[j]; };
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   const int total = NOPS * d.ndm;
   if (gid >= total) return;
@@ -145,8 +163,6 @@ __global__ void k_factor_check(const double* __restrict__ rc, const double* __re
   const int labs = dm / d.mt, n = dm - labs * d.mt;
   const double a = n * d.kt, b = labs * d.kz;
   const bool rev = (op != OP_P);
-  const int M = d.n_r - 1;
-  auto x0 = [](int j) { return 1.0 + 0.5 * sin(0.7 * j); };
   auto T = [&](int ip) -> double& { return tmp[(int64_t)ip * total + gid]; };
   // b = A x0 and the forward sweep, in the factor's row order
   double w[4] = {0.0, 0.0, 0.0, 0.0};
@@ -202,7 +218,7 @@ __global__ void k_factor_check(const double* __restrict__ rc, const double* __re
 
 hipError_t launch_factor_check(tc_ctx* c, double* tmp, unsigned long long* worst_dev) {
   const int total = NOPS * c->d.ndm;
-  hipLaunchKernelGGL(k_factor_check, dim3((total + 63) / 64), dim3(64), 0, c->stream, c->rc_dev, c->fac, c->d, tmp,
+  hipLaunchKernelGGL(k_factor_check, dim3((total + 63) / 64), dim3(64), c->d.n_r * sizeof(double), c->stream, c->rc_dev, c->fac, c->d, tmp,
                      worst_dev);
   return hipGetLastError();
 }

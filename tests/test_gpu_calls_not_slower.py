@@ -59,3 +59,23 @@ def test_diagnostics_of_large_planes(n_r, m_theta, m_z):
     print(f"{n_r} x {m_theta} x {m_z}: diagnostics {d * 1e6:.0f} us, finite check {f * 1e6:.0f} us")
     S.close()
     assert d <= 8 * f
+
+
+@pytest.mark.parametrize("n_r,m_theta,m_z", [(9, 512, 1024), (16, 512, 1024)])
+def test_set_up_of_the_line_copy(n_r, m_theta, m_z, monkeypatch):
+    # what the line kernels' copy of the factors adds to a context's set-up, as
+    # the rate at which its bytes are read and written: 1.4 and 1.5 TB/s
+    best, held = {}, {}
+    for _ in range(8):
+        for line in ("1", "0"):
+            monkeypatch.setenv("TC_PC_LINE", line)
+            t = time.perf_counter()
+            S = solver(n_r, m_theta, m_z)
+            t = time.perf_counter() - t
+            held[line] = S.memory_bytes()
+            S.close()
+            best[line] = min(best.get(line, t), t)
+    rate = 2 * (held["1"] - held["0"]) / (best["1"] - best["0"])
+    print(f"{n_r} x {m_theta} x {m_z}: set-up {best['1'] * 1e6:.0f} us, without the copy {best['0'] * 1e6:.0f} us, "
+          f"{rate / 1e12:.2f} TB/s")
+    assert rate >= 1.8e12
