@@ -275,8 +275,10 @@ tc_status tc_kernel_time(tc_ctx* ctx, int32_t which, double* ms_out, int32_t* la
 /* The factors are LU without pivoting (the paper's DGBTRF pivots; the
  * Neumann rows of P are scaled to the size of the Laplacian rows instead).
  * tc_init accepts them only after a check: for every operator and distinct
- * mode it solves A x = A x0 (x0_j = 1 + sin(0.7 j)/2) with the stored
- * factors and takes the componentwise backward error
+ * mode it solves A x = A x0 (x0_j = 1 + sin(0.7 j)/2), with the lane-contiguous
+ * copy of the factors and the kernels that use it where the context keeps one
+ * and with the factors themselves elsewhere, and takes the componentwise
+ * backward error
  * max_j |A x - b|_j / (|A| |x| + |b|)_j; above 1e-12 it fails with
  * TC_ESINGULAR.  This call returns the largest error found (host double). */
 tc_status tc_factor_backward_error(const tc_ctx* ctx, double* error_host);

@@ -843,14 +843,24 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
     free_ctx(c);
     return TC_ESINGULAR;
   }
+  // the line kernels' copy of the factors, where the grid allows them
+  // (TC_PC_LINE=0 selects the four-sweep kernels instead): the last allocation,
+  // left out where the device has no room for it
+  if (e = make_flin(c); e != hipSuccess) {
+    g_init_error = std::string("HIP error during set-up: ") + hipGetErrorString(e);
+    free_ctx(c);
+    return TC_EHIP;
+  }
   // the factors are unpivoted: check their backward error on one solve per
-  // operator and mode before accepting them
-  {
+  // operator and mode before accepting them, by the kernels that the steps use;
+  // a copy that failed would be given up and the factors themselves checked
+  for (;;) {
     unsigned long long* const worst = reinterpret_cast<unsigned long long*>(c->red);
     unsigned long long hw = 0;
     static_assert(NOPS * sizeof(double) <= 2 * sizeof(cd), "the check's work space fits one field of m_z = 2 |l| slots");
     e = hipMemsetAsync(worst, 0, sizeof(*worst), c->stream);
-    if (e == hipSuccess) e = launch_factor_check(c, reinterpret_cast<double*>(c->omega), worst);
+    if (e == hipSuccess)
+      e = c->flin ? launch_line_check(c, worst) : launch_factor_check(c, reinterpret_cast<double*>(c->omega), worst);
     if (e == hipSuccess) e = hipMemcpyAsync(&hw, worst, sizeof(hw), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
@@ -859,19 +869,11 @@ tc_status tc_init(const tc_grid* g, double eta, double Re_i, double Re_o, double
       return TC_EHIP;
     }
     std::memcpy(&c->factor_error, &hw, sizeof(double));
-    if (!(c->factor_error <= TC_FACTOR_CHECK_MAX)) {
-      g_init_error = "the unpivoted factors fail the backward-error check (" + std::to_string(c->factor_error) + ")";
-      free_ctx(c);
-      return TC_ESINGULAR;
-    }
-  }
-  // the line kernels' copy of the factors, where the grid allows them
-  // (TC_PC_LINE=0 selects the four-sweep kernels instead): last, and left out
-  // where the device has no room for it
-  if (hipError_t el = make_flin(c); el != hipSuccess) {
-    g_init_error = std::string("HIP error during set-up: ") + hipGetErrorString(el);
+    if (c->factor_error <= TC_FACTOR_CHECK_MAX) break;
+    if (drop_flin(c)) continue;
+    g_init_error = "the unpivoted factors fail the backward-error check (" + std::to_string(c->factor_error) + ")";
     free_ctx(c);
-    return TC_EHIP;
+    return TC_ESINGULAR;
   }
   // the allocation-free diagnostics' scratch address on this device
   if (hipGetDevice(&c->device) != hipSuccess || !scratch_address(c->device)) {

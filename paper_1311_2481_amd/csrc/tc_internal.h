@@ -164,7 +164,9 @@ hipError_t launch_factor(tc_ctx* c, int* bad_dev);
 // componentwise backward error of the stored factors on one solve per
 // operator and mode (tmp: n_r * 4 * ndm doubles of work space)
 hipError_t launch_factor_check(tc_ctx* c, double* tmp, unsigned long long* worst_dev);
-// largest backward error tc_init accepts from that check
+// the same on one solve by the line kernels, with their copy of the factors
+hipError_t launch_line_check(tc_ctx* c, unsigned long long* worst_dev);
+// largest backward error tc_init accepts from either check
 constexpr double TC_FACTOR_CHECK_MAX = 1e-12;
 hipError_t launch_solve(tc_ctx* c, int op, int transposed, const cd* rhs, cd* x);
 // transposed solve on grids without the line kernels (x must not alias rhs)
@@ -184,11 +186,12 @@ hipError_t launch_pc_line(tc_ctx* c, const cd* u, const cd* u_prev, const cd* N,
 // solves of nop operators from op0 on the line layout (x may alias rhs)
 hipError_t launch_solve_line(tc_ctx* c, int op0, int nop, int transposed, const cd* rhs, cd* x);
 // what the per-shape units (tc_line_*.hip) launch
-enum { LINE_PC, LINE_SOLVE, LINE_ADJ };
+enum { LINE_PC, LINE_SOLVE, LINE_ADJ, LINE_CHECK };
 struct LineArgs {
   int what, flag, op0, nop;
   const cd* in[4];
   cd* out[4];
+  unsigned long long* worst;
 };
 hipError_t run_line_2(tc_ctx* c, const LineArgs& x);
 hipError_t run_line_4(tc_ctx* c, const LineArgs& x);

@@ -136,6 +136,13 @@ hipError_t launch_solve_line(tc_ctx* c, int op0, int nop, int transposed, const 
   return run_line(c, LineArgs{LINE_SOLVE, transposed, op0, nop, {rhs}, {x}});
 }
 
+hipError_t launch_line_check(tc_ctx* c, unsigned long long* worst) {
+  LineArgs x{};
+  x.what = LINE_CHECK;
+  x.worst = worst;
+  return run_line(c, x);
+}
+
 hipError_t launch_pc_adj_line(tc_ctx* c, const cd* ub, const cd* nin, cd* out_u, cd* out_up, cd* out_np, cd* ntot) {
   return run_line(c, LineArgs{LINE_ADJ, 0, 0, 0, {ub, nin}, {out_u, out_up, out_np, ntot}});
 }

@@ -6,6 +6,7 @@
 #include <atomic>
 
 #include "tc_internal.h"
+#include "tc_solve_dev.h"
 
 namespace tc {
 namespace {
@@ -626,6 +627,76 @@ __global__ __launch_bounds__(WAVES * NLANE) void k_solve_l(const double* __restr
   }
 }
 
+// Backward error of the line solves: k_factor_check (tc_solve.hip) with the
+// copy of the factors and the sweeps across lanes that the other kernels here
+// use.  The right-hand side and the residual are formed on chip, so the kernel
+// reads the copy and little else.
+template <int LPS, int RPL>
+__global__ __launch_bounds__(WAVES * NLANE) void k_check_l(const double* __restrict__ rc, const double* __restrict__ flin,
+                                                          Dims d, unsigned long long* worst, int ntile, int per) {
+  using L = Line<LPS, RPL>;
+  extern __shared__ double x0s[];
+  const int M = d.n_r - 1;
+  for (int j = threadIdx.x; j <= M; j += blockDim.x) x0s[j] = 1.0 + 0.5 * sin(0.7 * j);
+  __syncthreads();
+  LineLane<LPS, RPL> q;
+  if (!q.make(d, ntile, per) || q.sign) return;  // the slots +l and -l share their factors
+  typename L::Solver sv;
+  sv.fl = flin + (int64_t)q.dmc * L::BLK + 2 * q.ch;
+  sv.fop = (int64_t)d.ndm * L::BLK;
+  sv.ch = q.ch;
+  double err = 0.0;
+  bool bad = false;
+#pragma unroll 1
+  for (int op = 0; op < NOPS; ++op) {
+    auto node = [&](int r) { return op == OP_P ? q.j0 + r : RPL * LPS - 1 - (q.j0 + r); };
+    typename L::Rows f;
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+      const int j = node(r);
+      double s = 0.0;
+      if (j <= M) {
+        double row[NB9];
+        operator_row(rc, d, op, j, q.a, q.b, row);
+#pragma unroll
+        for (int k = 0; k < NB9; ++k) {
+          const int i = j + k - HW;
+          if (i >= 0 && i <= M) s = fma(row[k], x0s[i], s);
+        }
+      }
+      f[r] = cd{s, 0.0};
+    }
+    double rhs[RPL];
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) rhs[r] = f[r].x;
+    sv.template prefetch<false>(op);
+    sv.template solve<false>(op, -1, f);
+    cd w[RPL + 2 * HW];
+    L::halo(f, w, q.ch);
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+      const int j = node(r);
+      if (j > M) continue;
+      double row[NB9];
+      operator_row(rc, d, op, j, q.a, q.b, row);
+      double s = 0.0, den = 0.0;
+#pragma unroll
+      for (int k = 0; k < NB9; ++k) {
+        const double x = op == OP_P ? w[r + k].x : w[r + 2 * HW - k].x;
+        s = fma(row[k], x, s);
+        den = fma(fabs(row[k]), fabs(x), den);
+      }
+      den += fabs(rhs[r]);
+      const double e = den > 0.0 ? fabs(s - rhs[r]) / den : 0.0;
+      bad = bad || !(e <= 1.0);
+      err = fmax(err, e);
+    }
+  }
+  if (bad) err = 1.0;  // a non-finite residual counts as the worst
+  for (int off = 32; off > 0; off >>= 1) err = fmax(err, __shfl_xor(err, off));
+  if (q.lane == 0) atomicMax(worst, (unsigned long long)__double_as_longlong(err));
+}
+
 // Adjoint of the predictor-corrector on the line layout: the chain of the
 // adjoint step (tc_adjoint.hip) from the cotangent u_bar' of u^{i+1} and
 // N_bar of N^i to the cotangents of u^i, u^{i-1}, N^{i-1} and the total
@@ -854,6 +925,10 @@ template <int LPS, int RPL> hipError_t run_pcl(tc_ctx* c, const LineArgs& x) {
     case LINE_SOLVE:
       hipLaunchKernelGGL((k_solve_l<LPS, RPL>), g.grid, g.block, 0, c->stream, c->flin, c->d, x.op0, x.nop, x.flag,
                          x.in[0], x.out[0], g.ntile, g.per);
+      break;
+    case LINE_CHECK:
+      hipLaunchKernelGGL((k_check_l<LPS, RPL>), g.grid, g.block, c->d.n_r * sizeof(double), c->stream, c->rc_dev, c->flin,
+                         c->d, x.worst, g.ntile, g.per);
       break;
     case LINE_ADJ:
       e = lds_limit<LPS, RPL, 3>(&k_pcl_adj<LPS, RPL>, adj_devices, c->device);
