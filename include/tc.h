@@ -286,6 +286,10 @@ tc_status tc_factor_backward_error(const tc_ctx* ctx, double* error_host);
 /* Bytes of device memory the context holds (host pointer out). */
 tc_status tc_memory_bytes(const tc_ctx* ctx, uint64_t* bytes_out);
 
+/* Of those, the bytes of the lane-contiguous copy of the factors (tc_init);
+ * 0 on a context that uses the four-sweep kernels. */
+tc_status tc_line_copy_bytes(const tc_ctx* ctx, uint64_t* bytes_out);
+
 #ifdef __cplusplus
 }
 #endif

@@ -44,7 +44,7 @@ EXPORTS = ["tc_init", "tc_destroy", "tc_last_error", "tc_radial_nodes", "tc_set_
            "tc_get_history", "tc_step", "tc_nonlinear", "tc_helmholtz_solve", "tc_helmholtz_solve_transposed",
            "tc_step_adjoint", "tc_perturbation_energy_gradient", "tc_adjoint_seed", "tc_adjoint_initial_history",
            "tc_control_velocity", "tc_control_gradient", "tc_control_ascent_update", "tc_get_diag", "tc_get_diag_noalloc", "tc_check_finite", "tc_set_timing", "tc_kernel_time", "tc_factor_backward_error",
-           "tc_memory_bytes"]
+           "tc_memory_bytes", "tc_line_copy_bytes"]
 
 
 def load_library(path=LIB_PATH):
@@ -81,6 +81,7 @@ def load_library(path=LIB_PATH):
     lib.tc_set_timing.argtypes = [vp, i32]
     lib.tc_kernel_time.argtypes = [vp, i32, ctypes.POINTER(dbl), ctypes.POINTER(i32)]
     lib.tc_memory_bytes.argtypes = [vp, ctypes.POINTER(ctypes.c_uint64)]
+    lib.tc_line_copy_bytes.argtypes = [vp, ctypes.POINTER(ctypes.c_uint64)]
     lib.tc_factor_backward_error.argtypes = [vp, ctypes.POINTER(dbl)]
     for name in EXPORTS:
         if name != "tc_last_error":
@@ -267,6 +268,13 @@ class Solver:
     def memory_bytes(self):
         b = ctypes.c_uint64()
         self._check(self.lib.tc_memory_bytes(self.ctx, ctypes.byref(b)))
+        return b.value
+
+    def line_copy_bytes(self):
+        """Of memory_bytes(), the line kernels' copy of the factors (0: the
+        context uses the four-sweep kernels)."""
+        b = ctypes.c_uint64()
+        self._check(self.lib.tc_line_copy_bytes(self.ctx, ctypes.byref(b)))
         return b.value
 
     def twin(self, stream):

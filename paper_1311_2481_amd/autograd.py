@@ -15,12 +15,19 @@ the adjoint steps of the current one, so with ``overlap`` a second context
 (``Solver.twin``, same grid and factors) recomputes it on a second stream,
 into the other of two segment buffers, while the current segment's adjoint
 steps run; events order the hand-offs.  The arithmetic is the same, so the
-gradient is the same bit for bit.  ``overlap=None`` takes it when the
-context holds at most 4 GiB (the twin doubles that).
+gradient is the same bit for bit (as long as both contexts have room for the
+line kernels' copy of the factors, or neither has it).  ``overlap=None`` takes
+it when the context holds at most 4 GiB beside that copy (the twin doubles what
+it holds).
 """
 import torch
 
 TWIN_MAX_BYTES = 4 << 30
+
+
+def overlaps(solver):
+    """Whether overlap=None takes the overlapped reverse sweep."""
+    return solver.memory_bytes() - solver.line_copy_bytes() <= TWIN_MAX_BYTES
 
 
 def _segment(solver, seg, start, end, cu, cup, cNp):
@@ -57,7 +64,7 @@ class TCSteps(torch.autograd.Function):
         J = solver.diag()["perturbation_energy"]
         ctx.solver, ctx.nsteps, ctx.every = solver, nsteps, every
         ctx.checkpoints, ctx.uT, ctx.u0 = checkpoints, uT, u0
-        ctx.overlap = solver.memory_bytes() <= TWIN_MAX_BYTES if overlap is None else bool(overlap)
+        ctx.overlap = overlaps(solver) if overlap is None else bool(overlap)
         return torch.tensor(J, dtype=torch.float64, device=u0.device)
 
     @staticmethod

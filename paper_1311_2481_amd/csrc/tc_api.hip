@@ -1100,4 +1100,10 @@ tc_status tc_memory_bytes(const tc_ctx* c, uint64_t* out) {
   return TC_OK;
 }
 
+tc_status tc_line_copy_bytes(const tc_ctx* c, uint64_t* out) {
+  if (!c || !out) return TC_EINVAL;
+  *out = c->flin ? c->flin_bytes : 0;
+  return TC_OK;
+}
+
 }  // extern "C"
