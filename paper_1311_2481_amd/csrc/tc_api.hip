@@ -626,6 +626,7 @@ namespace tc {
 
 hipError_t energy_of(tc_ctx* c, const cd* u, double& E) {
   const int nb = 1024;
+  std::lock_guard<std::mutex> lk(c->red_mutex);
   hipLaunchKernelGGL(k_energy, dim3(nb), dim3(256), 0, c->stream, c->d, u, c->diag_wr, c->red);
   hipError_t e = hipGetLastError();
   std::vector<double> h(nb, 0.0);
@@ -1002,6 +1003,7 @@ tc_status tc_helmholtz_solve_transposed(tc_ctx* c, tc_solve_kind k, const void* 
 
 tc_status tc_get_diag(tc_ctx* c, double* out) {
   if (!c || !out) return TC_EINVAL;
+  std::lock_guard<std::mutex> lk(c->red_mutex);
   return diag_of(c, c->red + TC_RED_DOUBLES, out, "tc_get_diag");
 }
 
@@ -1048,6 +1050,7 @@ tc_status tc_perturbation_energy_gradient(tc_ctx* c, const void* u, void* g) {
 
 tc_status tc_check_finite(tc_ctx* c) {
   if (!c) return TC_EINVAL;
+  std::lock_guard<std::mutex> lk(c->red_mutex);
   int* flag = reinterpret_cast<int*>(c->red);
   int h = 0;
   hipError_t e = hipMemsetAsync(flag, 0, sizeof(int), c->stream);

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -140,8 +141,11 @@ struct tc_ctx {
   unsigned int* zmax = nullptr;  // per-plane field magnitudes (ZMAX_WORDS n_r words)
   double* diag_wr = nullptr;     // trapezoid weight times r on every node
   double* diag_uc = nullptr;     // circular Couette u_theta on every node
-  // block partials of small reductions (TC_RED_DOUBLES), then those of tc_get_diag
+  // block partials of small reductions (TC_RED_DOUBLES), then those of
+  // tc_get_diag; red_mutex: held from the first launch that writes to it until
+  // its result is on the host
   double* red = nullptr;
+  std::mutex red_mutex;
   int device = -1;               // HIP device the context was created on
   double factor_error = 0.0;     // backward error of the factor check at tc_init
   int batch = 0;

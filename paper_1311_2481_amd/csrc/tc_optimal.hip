@@ -200,6 +200,7 @@ hipError_t control_velocity(tc_ctx* c, const cd* a, cd* u, bool with_couette) {
 // Host-side sums of <x, y>, <y, y>, <x, x> (synchronous).
 hipError_t control_dots(tc_ctx* c, const cd* x, const cd* y, double& xy, double& yy, double& xx) {
   const int64_t count = 12 * c->d.S;
+  std::lock_guard<std::mutex> lk(c->red_mutex);
   hipLaunchKernelGGL(k_control_dots, dim3(DOT_BLOCKS), dim3(256), 0, c->stream, count, x, y, c->red);
   hipError_t e = hipGetLastError();
   double h[3 * DOT_BLOCKS];
