@@ -258,26 +258,32 @@ template <typename T, int L> struct TShape {
   // thread holds of each spectrum (6, or 8 where the length is no multiple of
   // 6): as many as fit without a spill, or nearly (a few spilled registers
   // cost more than the wave they buy).  1: the compiler's choice.  At 6 points
-  // 1536 in float spills 2 registers for its sixth wave (399 us against 415 at
-  // five on 24 x 512 x 680), 1152 and 1920 would spill 12 and 14 (389 and 824
-  // us against 334 and 736); the adjoint at 1920 spills 24 for a third wave
-  // (whole adjoint step 6.24 ms against 5.75 at two).  The short FP64 lengths
-  // with 6 points a thread, or below 128 points, take three waves, with at most
-  // 6 registers spilled (80: 103 -> 89 us on 256 x 27 x 254; 160 would spill 11:
-  // 168 -> 183).
-  static constexpr bool LONG = L >= 1024, SIXPT = L % 6 == 0, F64 = sizeof(T) == 8;
-  static constexpr int EU = LONG ? (F64 ? (SIXPT ? 4 : 3) : (SIXPT ? (L % 512 == 0 ? 6 : 5) : 4)) : (F64 && (SIXPT || L < 128) ? 3 : 1);
-  static constexpr int EU_ADJ = LONG ? (SIXPT && L <= 1536 ? 3 : 2) : 1;
-  static constexpr int EU_CONV = L % 5 == 0 && !SIXPT ? 1 : 2;
+  // in float a last pass of 3-point butterflies (1536 = 8 8 8 3) spills 2
+  // registers for a sixth wave, one of 6 (1152, 1920) would spill 12 and 14: 1536
+  // 3.89 ms with six waves against 4.00 with five on 160 x 512 x 1024, 420
+  // against 437 us on 24 x 512 x 680; 1152 389 against 334, 1920 824 against 736.
+  // The adjoint's third wave at 6 points would spill 24 where a 5-point pass is
+  // among the others (1920: whole adjoint step 6.24 ms against 5.75 at two).  The
+  // short FP64 lengths with 6 points a thread, or below 128 points, take three
+  // waves, with at most 6 registers spilled (80: 103 -> 89 us on 256 x 27 x 254;
+  // 160 would spill 11: 168 -> 183).
+  static constexpr bool LONG = L >= 1024, SIXPT = L % 6 == 0, F64 = sizeof(T) == 8, FIVES = L % 5 == 0;
+  static constexpr RadixList RL = make_radices(L);
+  static constexpr int LAST = RL.r[RL.n - 1], BEFORE = RL.r[RL.n - 2];
+  static constexpr int EU = LONG ? (F64 ? (SIXPT ? 4 : 3) : (SIXPT ? (LAST == 3 ? 6 : 5) : 4))
+                                 : (F64 && (SIXPT || L < 128) ? 3 : 1);
+  static constexpr int EU_ADJ = LONG ? (SIXPT && !FIVES ? 3 : 2) : 1;
+  static constexpr int EU_CONV = FIVES && !SIXPT ? 1 : 2;
   // k_theta asks for its +- pairs one transform ahead, which takes at most 15
   // more registers, the peak being in the third transform.  Below 128 points
-  // they cost a wave per SIMD (64: 17.8 -> 19.6 us on 128 x 21 x 128), as they
-  // do at 576 (8 8 3 3: 48 -> 53 us on 21 x 192 x 128); the long lengths have
-  // none to spare.  288: 272 -> 256 us on 128 x 96 x 320 and 199 -> 190 us in
-  // float, 480: 262 -> 250 and 199 -> 183 us on 64 x 160 x 320; 192: even, in
-  // float 25 -> 24 us.  (The kernels of the adjoint and of the convective form
-  // spill or lose what they would gain.)
-  static constexpr bool AHEAD = L >= 128 && L < 1024 && L != 576;
+  // they cost a wave per SIMD (64: 17.8 -> 19.6 us on 128 x 21 x 128), as they do
+  // with two passes of 3 at the end, two butterflies a thread in either (576 = 8
+  // 8 3 3: 48 -> 53 us on 21 x 192 x 128); the long lengths have none to spare.
+  // 288: 272 -> 256 us on 128 x 96 x 320 and 199 -> 190 us in float, 480: 262 ->
+  // 250 and 199 -> 183 us on 64 x 160 x 320; 192: even, in float 25 -> 24 us.
+  // (The kernels of the adjoint and of the convective form spill or lose what
+  // they would gain.)
+  static constexpr bool AHEAD = L >= 128 && !LONG && !(LAST == 3 && BEFORE == 3);
   // row and place of a thread, and its row's LDS
   static __device__ __forceinline__ int row() { return WAVE ? threadIdx.x / TPF : threadIdx.x % RPB; }
   static __device__ __forceinline__ int place() { return WAVE ? threadIdx.x % TPF : threadIdx.x / RPB; }
