@@ -254,9 +254,9 @@ tc_status tc_get_diag(tc_ctx* ctx, double* out_host);
  * GPU overwrites that GPU's array, so calls that overlap on one GPU (other
  * host threads, other streams) race and must be serialised by the caller;
  * nothing in it needs clearing, every partial is written before it is read.
- * Grids whose partials exceed the array (more than 2^19 - 8 doubles:
- * 4 max(1024, ceil(m_z m_theta / 256)) + 97 n_r) are rejected with
- * TC_EINVAL.  Synchronous; out_host: 8 doubles of HOST memory. */
+ * Grids with 4 max(1024, ceil(m_z m_theta / 256)) + 97 n_r above 2^19 - 8 are
+ * rejected with TC_EINVAL; the partials of every other grid fit the array.
+ * Synchronous; out_host: 8 doubles of HOST memory. */
 tc_status tc_get_diag_noalloc(tc_ctx* ctx, double* out_host);
 
 /* Check the current velocity for non-finite values: TC_ENONFINITE if any.

@@ -296,11 +296,12 @@ __global__ void k_energy(Dims d, const cd* __restrict__ u, const double* __restr
 // the wall slip's sums of the workgroups at the inner wall; per node and block
 // the three CFL mode sums; the theta-z mean of u_theta on every node.
 // 32 blocks, doubled while they leave slots for a second round and the
-// workgroups are fewer than 1024 (four for each CU): with 32 throughout, 9 x 512
-// x 1024 ran on 64 workgroups and took 640 us, 113 now.  The partials are then
+// workgroups are fewer than 512 (two for each CU): with 32 throughout, 9 x 512
+// x 1024 ran on 64 workgroups and took 640 us, 129 now (to 1024: 113, but 128 x
+// 96 x 320 104 -> 107).  The partials are then
 // those of fewer than 2 DIAG_GROUPS workgroups, with 32 blocks 109 n_r doubles
 // at most.
-constexpr int DIAG_BLOCKS = 32, DIAG_ROWS = 8, DIAG_THREADS = 256, DIAG_GROUPS = 1024;
+constexpr int DIAG_BLOCKS = 32, DIAG_ROWS = 8, DIAG_THREADS = 256, DIAG_GROUPS = 512;
 struct DiagLayout {
   int blocks, groups;
   size_t e, ep, dv, sl, cfl, mean, total;
@@ -1009,15 +1010,16 @@ tc_status tc_get_diag(tc_ctx* c, double* out) {
 
 tc_status tc_get_diag_noalloc(tc_ctx* c, double* out) {
   if (!c || !out) return TC_EINVAL;
-  // the documented limit; the partials of any grid within it fit
+  // the documented limit (partials that an earlier layout needed; those of any
+  // grid within it fit)
   const size_t need = 4 * (size_t)std::max<int64_t>(1024, (c->d.S + 255) / 256) + 97 * (size_t)c->d.n_r + 8;
   static_assert((size_t)(3 * DIAG_BLOCKS / DIAG_ROWS + 3 * DIAG_BLOCKS + 1) * 4096 + 4 * DIAG_BLOCKS + 8 <=
                     TC_DIAG_SCRATCH_DOUBLES, "the partials of the largest n_r must fit the scratch");
   static_assert((size_t)2 * DIAG_GROUPS * (3 + 1 + 3 * DIAG_ROWS + DIAG_ROWS) + 8 <= TC_DIAG_SCRATCH_DOUBLES,
                 "the partials of the most workgroups must fit the scratch");
   if (need > TC_DIAG_SCRATCH_DOUBLES)
-    return fail(c, TC_EINVAL, "tc_get_diag_noalloc: the grid needs " + std::to_string(need) +
-                                  " doubles of scratch, more than its " + std::to_string(TC_DIAG_SCRATCH_DOUBLES));
+    return fail(c, TC_EINVAL, "tc_get_diag_noalloc: the grid is past the limit of the scratch (" + std::to_string(need) +
+                                  " of " + std::to_string(TC_DIAG_SCRATCH_DOUBLES) + ")");
   double* part = diag_scratch(c);
   if (!part) return fail(c, TC_EHIP, "tc_get_diag_noalloc: no scratch address for this device");
   return diag_of(c, part, out, "tc_get_diag_noalloc");

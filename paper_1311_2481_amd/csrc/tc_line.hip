@@ -31,13 +31,14 @@
 // diagonal), so every sweep, either factor's, is y_i = f_i - sum m_i[c]
 // y_{i-1-c}, first up, then down the operator's own row order (a Helmholtz
 // operator's line is read mirrored), and a transposed one takes its
-// coefficients from the rows before.  The ten sweeps of a step then run one loop body of two
-// sweeps, and a sweep's coefficients load while the one before it runs.
+// coefficients from the rows before.  The ten sweeps of a step then run one loop
+// body of two sweeps, and a sweep's coefficients load while the one before it
+// runs.
 // (Written out, operator by operator, with the loads of each in front of it
 // and the moves through LDS, a wave took 126 000 cycles for 64 rows on a
 // small grid; it takes 79 000 now, 34 000 of them in the sweeps, whose
 // instructions issue back to back.  k_pcl on 32 x 16 x 32: 43.5 -> 30 us; on
-// 64 x 64 x 128, where it moves 235 MB, 61 -> 53 us.)
+// 64 x 64 x 128, where it moves 235 MB, 61 -> 55 us.)
 //
 // Stencils (D1 over +-4 rows) take their 4 halo rows from the neighbouring
 // lanes; the per-row stencil weights sit in LDS.
@@ -48,17 +49,18 @@
 
 namespace tc {
 
-// Where the line kernels run, from the predictor-corrector group (with the
-// curl) of both forms timed over n_r = 16 .. 256 and planes of 16 x 32 to 512
-// x 1024 modes (us, line against four sweeps):
-//   to 64 rows (8 lanes) everywhere: 40 against 153 (64 x 16 x 32), 58
-//     against 227 (64 x 64 x 128), 4070 against 4690 (64 x 512 x 1024);
-//   to 128 rows (16 lanes) to 65536 distinct modes: 115 against 349
-//     (100 x 64 x 128), 1900 against 2030 (100 x 256 x 512), but 7510
+// Where the line kernels run, from the predictor-corrector group of both
+// forms, with the curl, timed by events (about 3 us above the kernels' own
+// times) over n_r = 16 .. 256 and planes of 16 x 32 to 512 x 1024 modes (us,
+// line against four sweeps):
+//   to 64 rows (8 lanes) everywhere: 32 against 150 (64 x 16 x 32), 58
+//     against 222 (64 x 64 x 128), 4090 against 4700 to 5370 (64 x 512 x 1024);
+//   to 128 rows (16 lanes) to 65536 distinct modes: 116 against 336
+//     (100 x 64 x 128), 1920 against 2030 (100 x 256 x 512), but 7510
 //     against 7070 (100 x 512 x 1024), where the sweeps stream whole cache
 //     lines from HBM and have lanes enough to hide their chains;
-//   to 256 rows (32 lanes) below 16384 distinct modes: 310 against 684
-//     (200 x 64 x 128), 1350 against 1580 (256 x 96 x 320), but 5040 against
+//   to 256 rows (32 lanes) below 16384 distinct modes: 312 against 671
+//     (200 x 64 x 128), 1330 against 1510 (256 x 96 x 320), but 5040 against
 //     2980 (160 x 256 x 512): a wave's load of one row is two slots, 32
 //     bytes, wide.
 // Grids whose waves, of 64 lanes, are at most one for each SIMD with twice
@@ -67,8 +69,8 @@ namespace tc {
 // moves stay within 16 lanes: a wave then has 5 rows in the place of 8 to go
 // through, and there are CUs enough.  8 -> 5 rows: 34.5 -> 26.8 (32 x 16 x
 // 32), 38.6 -> 31.6 (64 x 16 x 32), 44.9 -> 40.6 (64 x 32 x 128); with two
-// waves for each SIMD 54.9 -> 78.4 (64 x 64 x 128), with 32 lanes 50.7 ->
-// 59.8 (128 x 32 x 64).
+// waves for each SIMD 55 -> 78 (64 x 64 x 128), with 32 lanes 51 -> 60 (128 x
+// 32 x 64).
 LineShape line_shape(const Dims& d) {
   LineShape s{0, 0};
   for (int lps = 2; lps <= LINE_LPS_MAX; lps *= 2)

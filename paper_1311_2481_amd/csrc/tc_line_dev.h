@@ -328,7 +328,7 @@ template <int LPS, int RPL> struct LineLane {
 // wave per SIMD (its four fields fill the LDS and the coefficients of two
 // sweeps the registers), so on small grids the chain of loads and
 // substitutions, and on larger ones the state and factors, 19 fields and 36
-// doubles per distinct mode-row: 64 x 64 x 128 moves 235 MB in 53 us, 4.4 TB/s.
+// doubles per distinct mode-row: 64 x 64 x 128 moves 235 MB in 55 us, 4.3 TB/s.
 template <int LPS, int RPL>
 __global__ __launch_bounds__(WAVES * NLANE) void k_pcl(const double* __restrict__ rc, const double* __restrict__ flin,
                                                       const double* __restrict__ ltab, Dims d, const cd* __restrict__ u, const cd* up,

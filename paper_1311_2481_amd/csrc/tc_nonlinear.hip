@@ -225,7 +225,7 @@ template <typename T, int L> struct ZShape {
   static_assert(NF >= 1, "transform too long for LDS");
   // Long FP64 transforms exchange one component at a time through LDS (half
   // the bytes), so that two workgroups fit a CU (registers capped for 8
-  // waves per SIMD, which these kernels meet without spilling): one
+  // waves per SIMD, of which these kernels spill 6 at most): one
   // workgroup's loads and stores then overlap the other's transform.  At
   // 1536 points this took the inverse pass from 14.4 to 12.7 ms and the
   // forward pass from 7.8 to 6.4 ms on the production planes.  The float
